@@ -104,12 +104,13 @@ __device__ __forceinline__ unsigned xcd_block() {
 __device__ __forceinline__ float shfl_xor_f(float v, int m) { return __shfl_xor(v, m, kWave); }
 __device__ __forceinline__ int shfl_xor_i(int v, int m) { return __shfl_xor(v, m, kWave); }
 
-// Inclusive prefix sum over the wave of a 64-bit value.
-__device__ __forceinline__ int64_t wave_incl_scan(int64_t v) {
+// Inclusive prefix sum over the wave of a 32- or 64-bit integer.
+template <class T>
+__device__ __forceinline__ T wave_incl_scan(T v) {
     const int l = lane_id();
 #pragma unroll
     for (int d = 1; d < kWave; d <<= 1) {
-        int64_t o = __shfl_up(v, d, kWave);
+        T o = __shfl_up(v, d, kWave);
         if (l >= d) v += o;
     }
     return v;

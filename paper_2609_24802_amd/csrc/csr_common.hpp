@@ -39,7 +39,6 @@ constexpr int kUnroll = 4;
 constexpr int kBlock = 256;        // threads per block of the traversal kernels
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kPlanRowsPerThread = 8;
-constexpr int kPlanTile = kBlock * kPlanRowsPerThread;
 constexpr int kClasses = 3;        // chunk groups of 64, 32 and 16 lanes
 constexpr int kPlanVals = kClasses + 2;  // per tile: chunks of each class, partial slots, split rows
 
@@ -116,7 +115,7 @@ struct PlanCounts {
 };
 
 struct PlanBounds {
-    int64_t tiles, cap[kClasses], max_chunks, max_slots, max_splits;
+    int64_t cap[kClasses], max_chunks, max_slots, max_splits;
 };
 
 // Capacities: a chunk of class c holds more than lo_c edges (class 0: a full
@@ -125,7 +124,6 @@ struct PlanBounds {
 // every class-1 or class-2 chunk ends a distinct row.
 inline PlanBounds plan_bounds(int64_t nrows, int64_t nedges, const Geom &g) {
     PlanBounds b;
-    b.tiles = ceil_div(nrows > 0 ? nrows : 1, kPlanTile);
     for (int c = 0; c < kClasses; ++c) {
         int64_t cap = 0;
         if (c < g.nclass) {
@@ -257,6 +255,10 @@ struct Acc<K, RED_SUM> {
 #pragma unroll
         for (int k = 0; k < K; ++k) v[k] += p.v[k];
     }
+    __device__ __forceinline__ void merge(const Acc &o) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k] += o.v[k];
+    }
     __device__ __forceinline__ void shfl_combine(int m) {
 #pragma unroll
         for (int k = 0; k < K; ++k) v[k] += shfl_xor_f(v[k], m);
@@ -295,6 +297,10 @@ struct Acc<K, RED_MAX> {
     __device__ __forceinline__ void add_partial(const Vec<K> &p, const int (&pe)[K]) {
 #pragma unroll
         for (int k = 0; k < K; ++k) take(p.v[k], pe[k], k);
+    }
+    __device__ __forceinline__ void merge(const Acc &o) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) take(o.v[k], o.e[k], k);
     }
     __device__ __forceinline__ void shfl_combine(int m) {
 #pragma unroll

@@ -126,8 +126,15 @@ __global__ __launch_bounds__(kBlock) void direct_kernel(Trav t, float *__restric
     }
 }
 
-// Merge the partial states of split rows in chunk order: lane slot s folds
-// chunks s, s + S, ..., then the slots are combined by a fixed shuffle tree.
+// Merge the partial states of split rows with a fixed tree: lane slot s of a wavefront's S folds chunks
+// s, s + S, ... in order, kMergeBatch loads in flight, then the slots are combined by shuffles.  A row
+// of more than kHubSlots chunks per slot is folded by a whole block (slot s of its 4 S), whose
+// wavefronts are combined in order through LDS: folded by one wavefront with one load in flight, a
+// 1,250-chunk row kept the merge running for 129 us (16M-edge power-law graph, 64 features; 106 us for
+// 250 chunks of the 17-feature max).
+constexpr int kMergeBatch = 8;
+constexpr int kHubSlots = 2 * kMergeBatch;
+
 template <int K, int L, int RED>
 __global__ __launch_bounds__(kBlock) void merge_kernel(const Split *__restrict__ splits,
                                                        const PlanCounts *__restrict__ counts, int64_t fu,
@@ -136,40 +143,64 @@ __global__ __launch_bounds__(kBlock) void merge_kernel(const Split *__restrict__
                                                        float *__restrict__ out, int32_t *__restrict__ out_arg) {
     constexpr Geom g = make_geom(L);
     using A = Acc<K, RED>;
+    __shared__ A wsum[kWavesPerBlock][L];
     const int lane = lane_id();
-    const int64_t wave = static_cast<int64_t>(blockIdx.x) * kWavesPerBlock + threadIdx.x / kWave;
+    const int wv = uniform(static_cast<int>(threadIdx.x / kWave));
+    const int64_t wave = static_cast<int64_t>(blockIdx.x) * kWavesPerBlock + wv;
     const int64_t nwaves = static_cast<int64_t>(gridDim.x) * kWavesPerBlock;
     const int64_t n_split = static_cast<int64_t>(counts->ctr[kCtrSplits].v);
     const int s = lane / L;
     const int l = lane % L;
+    // chunks c0, c0 + step, ... of row d, unit u
+    auto fold = [&](const Split &d, int64_t u, int c0, int step, A &acc) __attribute__((always_inline)) {
+        for (int c = c0; c < d.nch; c += step * kMergeBatch) {
+            Vec<K> p[kMergeBatch];
+            int pe[kMergeBatch][K];
+#pragma unroll
+            for (int b = 0; b < kMergeBatch; ++b) {
+                const int cb = c + b * step;
+                const int64_t unit = (static_cast<int64_t>(d.slot0) + (cb < d.nch ? cb : c)) * fu + u;
+                p[b] = load_unit<K>(part_v, unit);
+                if constexpr (RED == RED_MAX) load_unit_i<K>(part_e, unit, pe[b]);
+            }
+#pragma unroll
+            for (int b = 0; b < kMergeBatch; ++b)
+                if (c + b * step < d.nch) acc.add_partial(p[b], pe[b]);
+        }
+    };
+    auto put = [&](const Split &d, int64_t u, A &acc) __attribute__((always_inline)) {
+        acc.finalize();
+        store_unit<K>(out, d.row * fu + u, acc.v);
+        if constexpr (RED == RED_MAX) store_unit_i<K>(out_arg, d.row * fu + u, acc.e);
+    };
     for (int64_t it = wave; it < n_split; it += nwaves) {
         const Split d = splits[it];
-        const int64_t row = d.row;
+        if (d.nch > kHubSlots * g.S) continue;
         for (int64_t fb = 0; fb < fu; fb += L) {
             const int64_t u = fb + l;
-            const bool uok = u < fu;
             A acc;
             acc.init();
-            if (uok) {
-                for (int c = s; c < d.nch; c += g.S) {
-                    const int64_t unit = (static_cast<int64_t>(d.slot0) + c) * fu + u;
-                    Vec<K> p = load_unit<K>(part_v, unit);
-                    int pe[K];
-                    if constexpr (RED == RED_MAX) {
-                        load_unit_i<K>(part_e, unit, pe);
-                    } else {
-#pragma unroll
-                        for (int k = 0; k < K; ++k) pe[k] = 0;
-                    }
-                    acc.add_partial(p, pe);
-                }
-            }
+            if (u < fu) fold(d, u, s, g.S, acc);
             reduce_lanes<L, kWave>(acc);
-            if (s == 0 && uok) {
-                acc.finalize();
-                store_unit<K>(out, row * fu + u, acc.v);
-                if constexpr (RED == RED_MAX) store_unit_i<K>(out_arg, row * fu + u, acc.e);
+            if (s == 0 && u < fu) put(d, u, acc);
+        }
+    }
+    for (int64_t it = blockIdx.x; it < n_split; it += gridDim.x) {
+        const Split d = splits[it];
+        if (d.nch <= kHubSlots * g.S) continue;   // the whole block agrees
+        for (int64_t fb = 0; fb < fu; fb += L) {
+            const int64_t u = fb + l;
+            A acc;
+            acc.init();
+            if (u < fu) fold(d, u, wv * g.S + s, g.S * kWavesPerBlock, acc);
+            reduce_lanes<L, kWave>(acc);
+            if (s == 0) wsum[wv][l] = acc;
+            __syncthreads();
+            if (wv == 0 && s == 0 && u < fu) {
+                for (int w = 1; w < kWavesPerBlock; ++w) acc.merge(wsum[w][l]);
+                put(d, u, acc);
             }
+            __syncthreads();
         }
     }
 }
