@@ -27,7 +27,8 @@
 //    evaluation is the cost, so the bound is taken before it.)
 #include "knn.hpp"
 
-#include "csr_bwd.hpp"
+#include "common.hpp"
+#include "radix.hpp"
 
 namespace tiga {
 namespace knn {
@@ -48,7 +49,7 @@ struct Ws {
     float *part;        // [kPartials][6] box partials
     float *box;         // [8]: lo xyz, hi xyz
     int32_t *key, *key_sorted, *perm;
-    void *sort;
+    radix::Ws sort;
     f4 *rec;            // [ntile * kTile] Morton-ordered (x, y, z, original index)
     f4 *tlo, *thi;      // [ntile] box of each tile's finite records
     f4 *slo, *shi;      // [ntile * kTile / 8] box of each run of 8 records (one candidate step)
@@ -63,7 +64,7 @@ Ws carve(Carve &c, int64_t n) {
     w.key = c.take<int32_t>(n);
     w.key_sorted = c.take<int32_t>(n);
     w.perm = c.take<int32_t>(n);
-    w.sort = c.take<char>(csr::sort_keys_ws_bytes(n));
+    w.sort = radix::carve(c, n);
     w.rec = c.take<f4>(ntile * kTile);
     w.tlo = c.take<f4>(ntile);
     w.thi = c.take<f4>(ntile);
@@ -555,9 +556,11 @@ int forward(int64_t n, int32_t feat, const float *pos, const float *x, int32_t k
         hipLaunchKernelGGL(morton_kernel, dim3(static_cast<unsigned>(ceil_div(n, kBlock))), dim3(kBlock), 0, stream,
                            pos, n, w.box, w.key);
         if (int rc = check_launch("kNN keys")) return rc;
-        if (int rc = csr::launch_sort_keys(w.key, n, int64_t{1} << (3 * kBits), w.key_sorted, w.perm, nullptr, w.sort,
-                                           stream))
-            return rc;
+        const radix::Shape s = radix::shape_for(n, int64_t{1} << (3 * kBits));
+        radix::Out out;
+        out.idx = w.perm;
+        if (int rc = radix::launch_first_hist(s, w.key, w.sort, stream)) return rc;
+        if (int rc = radix::launch_sort(s, w.key, w.sort, out, nullptr, stream)) return rc;
     }
     hipLaunchKernelGGL(records_kernel, dim3(static_cast<unsigned>(ceil_div(ntile * kTile, kBlock))), dim3(kBlock), 0,
                        stream, pos, w.perm, n, ntile * kTile, w.rec);

@@ -10,15 +10,13 @@
 // Consume: one wavefront per destination cell; the 27 neighbour cells are 9
 // contiguous runs of the cell-ordered arrays (x-adjacent cells are adjacent
 // in memory).
-#include "csr_bwd.hpp"
+#include "csr_common.hpp"
 #include "radius.hpp"
 #include "radius_cells.hpp"
+#include "radix.hpp"
 
 namespace tiga {
 namespace radius {
-
-using csr::launch_excl_scan;
-using csr::scan_ws_bytes;
 
 namespace {
 
@@ -67,46 +65,12 @@ __global__ __launch_bounds__(kBlock) void bbox_partial_kernel(const float *__res
     }
 }
 
-// One block: reduce the per-block boxes, then thread 0 picks the cell size and
-// the grid dimensions.
-__global__ __launch_bounds__(kBlock) void grid_params_kernel(const float *__restrict__ part, int nblocks, int64_t n,
-                                                             float radius, int64_t max_cells, double spacing_scale,
-                                                             Params *__restrict__ prm) {
-    float mn[3] = {__builtin_inff(), __builtin_inff(), __builtin_inff()};
-    float mx[3] = {-__builtin_inff(), -__builtin_inff(), -__builtin_inff()};
-    for (int b = threadIdx.x; b < nblocks; b += blockDim.x)
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            mn[a] = fminf(mn[a], part[b * 6 + a]);
-            mx[a] = fmaxf(mx[a], part[b * 6 + 3 + a]);
-        }
-#pragma unroll
-    for (int m = 1; m < kWave; m <<= 1)
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            mn[a] = fminf(mn[a], shfl_xor_f(mn[a], m));
-            mx[a] = fmaxf(mx[a], shfl_xor_f(mx[a], m));
-        }
-    __shared__ float sh[kBlock / kWave][6];
-    if (lane_id() == 0)
-        for (int a = 0; a < 3; ++a) {
-            sh[threadIdx.x / kWave][a] = mn[a];
-            sh[threadIdx.x / kWave][3 + a] = mx[a];
-        }
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    double lo[3], hi[3];
-    for (int a = 0; a < 3; ++a) {
-        lo[a] = sh[0][a];
-        hi[a] = sh[0][3 + a];
-        for (int w = 1; w < kBlock / kWave; ++w) {
-            lo[a] = fmin(lo[a], static_cast<double>(sh[w][a]));
-            hi[a] = fmax(hi[a], static_cast<double>(sh[w][3 + a]));
-        }
-    }
+// Cell size and grid dimensions for the box [lo, hi] (one thread).
+__device__ __forceinline__ Params grid_params(const float (&lo)[3], const float (&hi)[3], int64_t n, float radius,
+                                              int64_t max_cells, double spacing_scale) {
     double ext[3], vol = 1.0;
     for (int a = 0; a < 3; ++a) {
-        ext[a] = hi[a] - lo[a];
+        ext[a] = static_cast<double>(hi[a]) - static_cast<double>(lo[a]);
         if (!(ext[a] >= 0.0)) ext[a] = 0.0;
         vol *= ext[a];
     }
@@ -133,43 +97,69 @@ __global__ __launch_bounds__(kBlock) void grid_params_kernel(const float *__rest
         d[0] = d[1] = d[2] = 1;
         h = 1.0 + ext[0] + ext[1] + ext[2];
     }
+    Params p;
     for (int a = 0; a < 3; ++a) {
-        prm->lo[a] = lo[a];
-        prm->dim[a] = static_cast<int>(d[a]);
+        p.lo[a] = static_cast<double>(lo[a]);
+        p.dim[a] = static_cast<int>(d[a]);
     }
-    prm->inv_h = 1.0 / h;
-    prm->ncell = static_cast<int>(d[0] * d[1] * d[2]);
+    p.inv_h = 1.0 / h;
+    p.ncell = static_cast<int>(d[0] * d[1] * d[2]);
+    return p;
 }
 
-// Cell coordinate along axis a, clamped to [0, dim - 1] before conversion
-// (NaN and -inf go to 0, +inf to the last cell).
-
-// Cell id of every point (z-major, x fastest).
-__global__ __launch_bounds__(kBlock) void cell_key_kernel(const float *__restrict__ pos, int64_t n,
-                                                          const Params *__restrict__ prm, int32_t *__restrict__ cell) {
-    const Params p = *prm;
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += stride) {
+// Cell id of every point (z-major, x fastest) and the sort's first histogram.  Every block reduces the
+// box partials and forms the grid parameters for itself (the same in all of them): 6 KB of reads and
+// about a microsecond of one thread, where a launch of its own cost 4.6 us; block 0 stores them.
+template <int ITEMS>
+__global__ __launch_bounds__(radix::kThreads) void cell_key_kernel(const float *__restrict__ pos, int64_t n,
+                                                                   const float *__restrict__ part, int nparts,
+                                                                   float radius, int64_t max_cells,
+                                                                   double spacing_scale, int rb,
+                                                                   Params *__restrict__ prm,
+                                                                   int32_t *__restrict__ cell,
+                                                                   uint32_t *__restrict__ counts) {
+    __shared__ uint32_t hist[radix::kMaxDigits];
+    __shared__ float sh[radix::kWaves][6];
+    __shared__ Params sp;
+    float mn[3] = {__builtin_inff(), __builtin_inff(), __builtin_inff()};
+    float mx[3] = {-__builtin_inff(), -__builtin_inff(), -__builtin_inff()};
+    for (int b = threadIdx.x; b < nparts; b += radix::kThreads)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            mn[a] = fminf(mn[a], part[b * 6 + a]);
+            mx[a] = fmaxf(mx[a], part[b * 6 + 3 + a]);
+        }
+#pragma unroll
+    for (int m = 1; m < kWave; m <<= 1)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            mn[a] = fminf(mn[a], shfl_xor_f(mn[a], m));
+            mx[a] = fmaxf(mx[a], shfl_xor_f(mx[a], m));
+        }
+    if (lane_id() == 0)
+        for (int a = 0; a < 3; ++a) {
+            sh[threadIdx.x / kWave][a] = mn[a];
+            sh[threadIdx.x / kWave][3 + a] = mx[a];
+        }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < radix::kWaves; ++w)
+            for (int a = 0; a < 3; ++a) {
+                mn[a] = fminf(mn[a], sh[w][a]);
+                mx[a] = fmaxf(mx[a], sh[w][3 + a]);
+            }
+        sp = grid_params(mn, mx, n, radius, max_cells, spacing_scale);
+        if (blockIdx.x == 0) *prm = sp;
+    }
+    __syncthreads();
+    const Params p = sp;
+    radix::key_tile<ITEMS>(n, rb, cell, counts, hist, [&](int64_t i) {
         const int cx = cell_axis(p, 0, pos[i * 3 + 0]);
         const int cy = cell_axis(p, 1, pos[i * 3 + 1]);
         const int cz = cell_axis(p, 2, pos[i * 3 + 2]);
-        cell[i] = (cz * p.dim[1] + cy) * p.dim[0] + cx;
-    }
+        return (cz * p.dim[1] + cy) * p.dim[0] + cx;
+    });
 }
-
-// Cell-ordered records (position, point id).
-__global__ __launch_bounds__(kBlock) void gather_records_kernel(const int32_t *__restrict__ perm, int64_t n,
-                                                                const float *__restrict__ pos,
-                                                                float4 *__restrict__ rec) {
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-    for (int64_t s = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; s < n; s += stride) {
-        const int32_t i = perm[s];
-        rec[s] = make_float4(pos[i * 3 + 0], pos[i * 3 + 1], pos[i * 3 + 2], __int_as_float(i));
-    }
-}
-
-
-
 
 // ---------------------------------------------------------------------------
 // Consume: one wavefront per destination cell.
@@ -232,26 +222,31 @@ __device__ __forceinline__ int64_t take_visit(uint32_t *__restrict__ sched, int 
     return __builtin_amdgcn_readfirstlane(v);
 }
 
-// order[rank(c)] = c for every cell c: the rank counts the cells of the whole
-// slabs, brick rows and bricks before c's, then c's place inside its brick.
-// Also clears the XCD counters of the consuming kernel that follows.
-__global__ __launch_bounds__(kBlock) void visit_order_kernel(const Params *__restrict__ prm,
-                                                            int32_t *__restrict__ order,
-                                                            uint32_t *__restrict__ sched) {
-    if (blockIdx.x == 0)
+// start[c] = first cell-ordered position of cell c (binary search over the sorted cell ids), and for the
+// cell-consuming kernels the visit order: order[rank(c)] = c, where the rank counts the cells of the
+// whole slabs, brick rows and bricks before c's, then c's place inside its brick.  Also clears the XCD
+// counters of the consuming kernel that follows.
+__global__ __launch_bounds__(kBlock) void cells_kernel(const Params *__restrict__ prm,
+                                                       const int32_t *__restrict__ sorted, int64_t n,
+                                                       int64_t *__restrict__ start, int32_t *__restrict__ order,
+                                                       uint32_t *__restrict__ sched) {
+    if (sched && blockIdx.x == 0)
         for (int i = threadIdx.x; i < kXcds * kCtrPerXcd * kSchedStride; i += kBlock) sched[i] = 0u;
     const Params p = *prm;
-    const int64_t X = p.dim[0], Y = p.dim[1], Z = p.dim[2];
-    for (int64_t c = blockIdx.x * static_cast<int64_t>(kBlock) + threadIdx.x; c < p.ncell;
+    const int X = p.dim[0], Y = p.dim[1], Z = p.dim[2];
+    for (int64_t c = blockIdx.x * static_cast<int64_t>(kBlock) + threadIdx.x; c <= p.ncell;
          c += static_cast<int64_t>(gridDim.x) * kBlock) {
-        const int64_t cx = c % X, cy = (c / X) % Y, cz = c / (X * Y);
-        const int64_t x0 = cx & ~static_cast<int64_t>(kBrick - 1), y0 = cy & ~static_cast<int64_t>(kBrick - 1),
-                      z0 = cz & ~static_cast<int64_t>(kBrick - 1);
+        start[c] = radix::lower_bound(sorted, n, c);
+        if (!order || c == p.ncell) continue;
+        // ncell < 2^31: 32-bit divisions
+        const int ci = static_cast<int>(c), cx = ci % X, cyz = ci / X, cy = cyz % Y, cz = cyz / Y;
+        const int x0 = cx & ~(kBrick - 1), y0 = cy & ~(kBrick - 1), z0 = cz & ~(kBrick - 1);
         const int64_t h = Z - z0 < kBrick ? Z - z0 : kBrick;
         const int64_t wy = Y - y0 < kBrick ? Y - y0 : kBrick;
         const int64_t wx = X - x0 < kBrick ? X - x0 : kBrick;
-        const int64_t rank = z0 * X * Y + y0 * h * X + x0 * h * wy + (cz - z0) * wy * wx + (cy - y0) * wx + (cx - x0);
-        order[rank] = static_cast<int32_t>(c);
+        const int64_t rank = static_cast<int64_t>(z0) * X * Y + y0 * h * X + x0 * h * wy + (cz - z0) * wy * wx +
+                             (cy - y0) * wx + (cx - x0);
+        order[rank] = ci;
     }
 }
 
@@ -757,17 +752,16 @@ struct Ws {
     Params *prm;
     float *bbox;
     int32_t *cell, *cell_sorted;
-    int32_t *perm_b;  // point id at each cell-ordered position
     int64_t *start;   // max_cells + 1 cell boundaries in cell order
     int32_t *order;   // max_cells: the cell visit order of the consuming kernels
     uint32_t *sched;  // the consuming kernels' per-XCD cell counters
     float4 *rec;
-    void *sort;
-    void *scan;
+    radix::Ws sort;
     uint32_t *flag;
     int64_t max_cells;
-    int bbox_blocks;
 };
+
+constexpr int kBoxBlocks = 256;   // box partials: every block of the key kernel reads them all
 
 // cells_per_point bounds the directory (max_cells = cells_per_point * n + 64): 1 for volume
 // clouds; more for callers whose points lie on surfaces, where the volume-based spacing floor
@@ -775,18 +769,15 @@ struct Ws {
 Ws carve(Carve &c, int64_t n, int64_t cells_per_point = 1) {
     Ws w;
     w.max_cells = cells_per_point * n + 64;
-    w.bbox_blocks = 1024;
     w.prm = c.take<Params>(1);
-    w.bbox = c.take<float>(6 * w.bbox_blocks);
+    w.bbox = c.take<float>(6 * kBoxBlocks);
     w.cell = c.take<int32_t>(n);
     w.cell_sorted = c.take<int32_t>(n);
-    w.perm_b = c.take<int32_t>(n);
     w.start = c.take<int64_t>(w.max_cells + 1);
     w.order = c.take<int32_t>(w.max_cells);
     w.sched = c.take<uint32_t>(kXcds * kCtrPerXcd * kSchedStride);
     w.rec = c.take<float4>(n);
-    w.sort = c.take<char>(csr::sort_keys_ws_bytes(n));
-    w.scan = c.take<char>(scan_ws_bytes(n + 1));
+    w.sort = radix::carve(c, n);
     w.flag = c.take<uint32_t>(1);
     return w;
 }
@@ -797,31 +788,28 @@ int blocks_for(int64_t n) {
     return static_cast<int>(b < cap ? b : cap);
 }
 
-// Build the cell directory and the cell-ordered records.
-int build(int64_t n, const float *pos, float radius, Ws &w, hipStream_t stream, double spacing_scale = 1.0) {
-    int nb = w.bbox_blocks;
-    const int64_t need = ceil_div(n, kBlock);
-    if (need < nb) nb = static_cast<int>(need);
+// Build the cell directory and the cell-ordered records; with `consume` also the cell visit order and
+// cleared counters of the cell-consuming kernels.
+int build(int64_t n, const float *pos, float radius, Ws &w, hipStream_t stream, bool consume,
+          double spacing_scale = 1.0) {
+    const int nb = static_cast<int>(ceil_div(n, kBlock) < kBoxBlocks ? ceil_div(n, kBlock) : kBoxBlocks);
     hipLaunchKernelGGL(bbox_partial_kernel, dim3(nb), dim3(kBlock), 0, stream, pos, n, w.bbox);
     if (int rc = check_launch("radius bbox")) return rc;
-    hipLaunchKernelGGL(grid_params_kernel, dim3(1), dim3(kBlock), 0, stream, w.bbox, nb, n, radius, w.max_cells,
-                       spacing_scale, w.prm);
-    if (int rc = check_launch("radius grid")) return rc;
     // cell-ordered positions: a stable sort by cell keeps ascending point ids
     // within a cell, so every candidate order depends only on the input
-    hipLaunchKernelGGL(cell_key_kernel, dim3(blocks_for(n)), dim3(kBlock), 0, stream, pos, n, w.prm, w.cell);
+    const radix::Shape s = radix::shape_for(n, w.max_cells);
+    auto *kern = s.items == 2 ? cell_key_kernel<2> : s.items == 4 ? cell_key_kernel<4> : cell_key_kernel<8>;
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(s.tiles)), dim3(radix::kThreads), 0, stream, pos, n, w.bbox,
+                       nb, radius, w.max_cells, spacing_scale, s.rb, w.prm, w.cell, w.sort.counts);
     if (int rc = check_launch("radius cell keys")) return rc;
-    if (int rc = csr::launch_sort_keys(w.cell, n, w.max_cells, w.cell_sorted, w.perm_b, w.start, w.sort, stream))
-        return rc;
-    hipLaunchKernelGGL(gather_records_kernel, dim3(blocks_for(n)), dim3(kBlock), 0, stream, w.perm_b, n, pos, w.rec);
-    return check_launch("radius records");
-}
-
-// The cell visit order and cleared counters of the consuming kernels (after build).
-int visit_order(const Ws &w, hipStream_t stream) {
-    hipLaunchKernelGGL(visit_order_kernel, dim3(blocks_for(w.max_cells)), dim3(kBlock), 0, stream, w.prm, w.order,
-                       w.sched);
-    return check_launch("radius visit order");
+    radix::Out out;
+    out.keys = w.cell_sorted;
+    out.pos = pos;
+    out.rec = w.rec;
+    if (int rc = radix::launch_sort(s, w.cell, w.sort, out, nullptr, stream)) return rc;
+    hipLaunchKernelGGL(cells_kernel, dim3(blocks_for(w.max_cells + 1)), dim3(kBlock), 0, stream, w.prm, w.cell_sorted,
+                       n, w.start, consume ? w.order : nullptr, consume ? w.sched : nullptr);
+    return check_launch("radius cells");
 }
 
 // Persistent grid for the cell kernels: a multiple of 8 blocks (one share
@@ -904,7 +892,7 @@ int forward(int64_t n, int32_t feat, const float *pos, const float *x, float rad
         // no features: the relation's counts only
         Carve c(ws);
         Ws w = carve(c, n);
-        if (int rc = build(n, pos, radius, w, stream)) return rc;
+        if (int rc = build(n, pos, radius, w, stream, false)) return rc;
         hipLaunchKernelGGL(neighbor_count_kernel, dim3(static_cast<unsigned>(ceil_div(n, kBlock))), dim3(kBlock), 0,
                            stream, w.prm, w.start, w.rec, n, radius * radius, count);
         return check_launch("radius counts");
@@ -915,8 +903,7 @@ int forward(int64_t n, int32_t feat, const float *pos, const float *x, float rad
     if (int rc = check_units(n, fu)) return rc;
     Carve c(ws);
     Ws w = carve(c, n);
-    if (int rc = build(n, pos, radius, w, stream)) return rc;
-    if (int rc = visit_order(w, stream)) return rc;
+    if (int rc = build(n, pos, radius, w, stream, true)) return rc;
     const float r2 = radius * radius;
     const float nis = -1.0f / (sigma * sigma) * kLog2e;  // weights are exp2(d2 * nis)
     if (vec) return fwd_units<4>(fu, w, x, r2, nis, y, count, stream);
@@ -930,8 +917,7 @@ int backward(int64_t n, int32_t feat, const float *pos, const float *x, float ra
     if (int rc = check_units(n, fu)) return rc;
     Carve c(ws);
     Ws w = carve(c, n);
-    if (int rc = build(n, pos, radius, w, stream)) return rc;
-    if (int rc = visit_order(w, stream)) return rc;
+    if (int rc = build(n, pos, radius, w, stream, true)) return rc;
     const float r2 = radius * radius;
     const float nis = -1.0f / (sigma * sigma) * kLog2e;  // weights are exp2(d2 * nis)
     const float tis = 2.0f / (sigma * sigma);
@@ -962,7 +948,7 @@ size_t cells_ws_bytes(int64_t n) {
 int build_cells(int64_t n, const float *pos, float radius, void *ws, Cells &out, hipStream_t stream) {
     Carve c(ws);
     Ws w = carve(c, n, kSharedCellsPerPoint);
-    if (int rc = build(n, pos, radius, w, stream, kSharedSpacingScale)) return rc;
+    if (int rc = build(n, pos, radius, w, stream, false, kSharedSpacingScale)) return rc;
     out.prm = w.prm;
     out.start = w.start;
     out.rec = w.rec;
@@ -973,7 +959,7 @@ int neighbors(int64_t n, const float *pos, float radius, const int64_t *nbr_ptr,
               hipStream_t stream) {
     Carve c(ws);
     Ws w = carve(c, n);
-    if (int rc = build(n, pos, radius, w, stream)) return rc;
+    if (int rc = build(n, pos, radius, w, stream, false)) return rc;
     if (int rc = fill_u32(w.flag, 0u, 1, stream)) return rc;
     const dim3 grid(static_cast<unsigned>(ceil_div(n, kBlock)));
     hipLaunchKernelGGL(neighbor_fill_kernel, grid, dim3(kBlock), 0, stream, w.prm, w.start, w.rec, n, radius * radius,
