@@ -1,0 +1,48 @@
+"""GPU parity of the kNN paths behind the cell directory: the cell select, the wider scan of queries near
+the faces of the cloud, and the tiled select of what both leave open, at the sizes and clouds where a
+query changes from one to the next.  Neighbour lists are exact."""
+import numpy as np
+import pytest
+
+from paper_2609_24802_amd import synth
+from tests.test_gpu_knn import check, cloud
+
+pytestmark = pytest.mark.gpu
+
+
+def points(kind, n):
+    rng = np.random.default_rng(n)
+    if kind == "box":         # a long box: the longest axis sets the table, most cells are empty
+        return (rng.random((n, 3)) * [40.0, 1.0, 0.02]).astype(np.float32)
+    if kind == "outlier":     # one far point: everything else shares a cell
+        p = rng.random((n, 3)).astype(np.float32)
+        p[17] = [1e4, -3e4, 5.0]
+        return p
+    if kind == "same":        # coincident points, and a few others
+        p = np.full((n, 3), 0.25, np.float32)
+        p[:40] = rng.random((40, 3))
+        return p
+    if kind == "far":         # coordinates whose spacing is a large part of a cell
+        return (1000.0 + rng.random((n, 3)) * 0.02).astype(np.float32)
+    if kind == "tiny":        # squared distances that underflow
+        return (rng.random((n, 3)) * 1e-22).astype(np.float32)
+    if kind == "holes":       # non-finite points among the others
+        p = rng.random((n, 3)).astype(np.float32)
+        p[rng.integers(0, n, 50), rng.integers(0, 3, 50)] = rng.choice([np.nan, np.inf, -np.inf], 50)
+        return p
+    if kind == "lattice":     # more than 64 equal distances at many keys
+        return synth.binary_grid_points(n, 3, (98, n), span=20)
+    return cloud(kind, n, 3)
+
+
+@pytest.mark.parametrize("kind", ["uniform", "box", "outlier", "same", "far", "tiny", "holes", "lattice", "line",
+                                  "grid", "cluster", "flat"])
+@pytest.mark.parametrize("k", [1, 16, 32])
+def test_clouds(lib, kind, k):
+    check(lib, points(kind, 7300), 1, k)
+
+
+@pytest.mark.parametrize("n", [7168, 7169, 7176, 9001])
+@pytest.mark.parametrize("k,F", [(0, 1), (5, 0), (17, 9), (31, 3)])
+def test_sizes(lib, n, k, F):
+    check(lib, points("uniform", n), F, k)
