@@ -184,7 +184,10 @@ __global__ __launch_bounds__(kThreads) void scatter_kernel(const int32_t *__rest
                 if (out.idx) out.idx[pos] = i;
                 if (out.rec) {
                     const float *p = out.pos + static_cast<int64_t>(i) * 3;
-                    out.rec[pos] = make_float4(p[0], p[1], p[2], __int_as_float(i));
+                    // a point with a non-finite coordinate is within the radius of, and near, nothing: all +inf
+                    const bool ok = __builtin_isfinite(p[0]) && __builtin_isfinite(p[1]) && __builtin_isfinite(p[2]);
+                    const float inf = __builtin_inff();
+                    out.rec[pos] = make_float4(ok ? p[0] : inf, ok ? p[1] : inf, ok ? p[2] : inf, __int_as_float(i));
                 }
             }
         }

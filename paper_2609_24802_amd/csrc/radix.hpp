@@ -74,7 +74,7 @@ inline Ws carve(Carve &c, int64_t n) {
 }
 
 // Results: sorted keys (null: not kept), the input position of each (null: not kept), and with `rec`
-// cell-ordered records (x, y, z of pos, input position as bits).
+// cell-ordered records (x, y, z of pos, all +inf if one of them is not finite; input position as bits).
 struct Out {
     int32_t *keys = nullptr;
     int32_t *idx = nullptr;

@@ -1,0 +1,114 @@
+"""GPU parity of the radius kernels on tiles of 16 destinations: row widths around the dispatch's bounds, partial
+tiles, tiles that cross rows of cells, more candidates than one pass holds, non-finite rows and denormals."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from tests.parity import assert_terms_close
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def host(t):
+    return t.cpu().numpy()
+
+
+def check(lib, pos, F, r, sigma, seed=0, offset=0):
+    n = pos.shape[0]
+    rng = np.random.default_rng(seed + F)
+    x, dy = (rng.standard_normal((n, F)).astype(np.float32) for _ in range(2))
+
+    def put(a):   # a contiguous copy that starts `offset` floats past an aligned address
+        t = torch.empty(a.size + offset, dtype=torch.float32, device="cuda")[offset:].view(a.shape)
+        return t.copy_(dev(a))
+
+    y, cnt = lib.tiga_mp_radius_fwd(dev(pos), put(x), r, sigma)
+    dx, dp = lib.tiga_mp_radius_bwd(dev(pos), put(x), put(dy), r, sigma)
+    dx1, _ = lib.tiga_mp_radius_bwd(dev(pos), put(x), put(dy), r, sigma, want_dpos=False)
+    _, dp1 = lib.tiga_mp_radius_bwd(dev(pos), put(x), put(dy), r, sigma, want_dx=False)
+    ry, rya, rc = oracle.radius_fwd(pos, x, r, sigma)
+    rdx, rdxa, rdp, rdpa = oracle.radius_bwd(pos, x, dy, r, sigma)
+    assert np.array_equal(host(cnt), rc)
+    assert_terms_close(host(y), ry, rya, what="y")
+    for a in (dx, dx1):
+        assert_terms_close(host(a), rdx, rdxa, what="dx")
+    for a in (dp, dp1):
+        assert_terms_close(host(a), rdp, rdpa, what="dpos")
+
+
+@pytest.mark.parametrize("F", [1, 2, 3, 4, 5, 8, 9, 15, 16, 17, 18, 31, 32, 33, 36, 50, 63, 64, 65])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_widths(lib, F, offset):
+    pos = np.random.default_rng(1).random((700, 3)).astype(np.float32)
+    check(lib, pos, F, 0.15, 0.08, offset=offset)
+
+
+@pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 31, 33, 64, 65, 129])
+def test_sizes(lib, n):
+    pos = np.random.default_rng(n).random((n, 3)).astype(np.float32)
+    for F in (1, 6, 32):
+        check(lib, pos, F, 0.4, 0.3)
+
+
+@pytest.mark.parametrize("kind", ["thin", "dense", "line", "grid"])
+def test_clouds(lib, kind):
+    rng = np.random.default_rng(4)
+    pos = rng.random((900, 3)).astype(np.float32)
+    r = 0.12
+    if kind == "thin":       # one or two points per row of cells: a tile has many segments
+        pos *= np.float32([0.2, 3.0, 3.0])
+    elif kind == "dense":    # several hundred candidates per tile: more than one pass
+        pos[:600] = pos[:600] * np.float32(0.2) + np.float32(0.4)
+    elif kind == "line":
+        pos[:, 1:] = 0.5
+    else:                    # coincident points and distances equal to the radius
+        pos = (rng.integers(0, 9, (900, 3)) / 8).astype(np.float32)
+        r = 0.125
+    for F in (1, 7, 32):
+        check(lib, pos, F, r, 0.1)
+
+
+@pytest.mark.parametrize("F", [1, 8, 32, 64])
+def test_non_finite_rows_reach_their_neighbours_only(lib, F):
+    rng = np.random.default_rng(5)
+    n, r, sigma = 500, 0.15, 0.1
+    pos = rng.random((n, 3)).astype(np.float32)
+    x, dy = (rng.standard_normal((n, F)).astype(np.float32) for _ in range(2))
+    pos[7, 1] = np.nan
+    bx, by = x.copy(), dy.copy()
+    bx[100], by[200] = np.inf, np.nan
+    y, _ = lib.tiga_mp_radius_fwd(dev(pos), dev(bx), r, sigma)
+    ry, rya, rc = oracle.radius_fwd(pos, x, r, sigma)
+    with np.errstate(all="ignore"):
+        near = ((pos[None] - pos[:, None]) ** 2).sum(-1) < np.float32(r) ** 2
+    np.fill_diagonal(near, False)
+    far = ~near[:, 100]
+    assert_terms_close(host(y)[far], ry[far], rya[far], what="y")
+    assert np.all(host(y)[near[:, 100]] == np.inf)
+    if F > 32:
+        return
+    dx, dp = lib.tiga_mp_radius_bwd(dev(pos), dev(bx), dev(by), r, sigma)
+    rdx, rdxa, rdp, rdpa = oracle.radius_bwd(pos, x, dy, r, sigma)
+    far = ~near[:, 200]
+    assert_terms_close(host(dx)[far], rdx[far], rdxa[far], what="dx")
+    assert np.all(np.isnan(host(dx)[near[:, 200]]))
+    far = ~(near[:, 100] | near[:, 200])
+    far[[100, 200]] = False
+    assert_terms_close(host(dp)[far], rdp[far], rdpa[far], what="dpos")
+
+
+@pytest.mark.parametrize("F", [1, 16, 32])
+def test_denormal_rows(lib, F):
+    # sigma so large that every weight is 1: sums of multiples of the smallest float are exact
+    rng = np.random.default_rng(6)
+    pos = rng.random((400, 3)).astype(np.float32)
+    k = rng.integers(-50, 50, (400, F))
+    x = (k * 2.0 ** -149).astype(np.float32)
+    y, _ = lib.tiga_mp_radius_fwd(dev(pos), dev(x), 0.2, 1e18)
+    ry, _, _ = oracle.radius_fwd(pos, x, 0.2, 1e18)
+    assert np.array_equal(host(y).astype(np.float64), ry)
