@@ -4,8 +4,9 @@
 // with N(i) the radius relation (j != i, fp32 squared distance strictly below fl(r*r)).
 //
 // MI355X design: a persistent grid of wavefronts walks the cell-ordered points, one point per
-// wavefront at a time.  Lanes are (neighbour slot, hidden unit): HP lanes per neighbour (HP >= the
-// hidden width, a power of two), 64 / HP neighbours per step.  Each lane keeps its row of W1 and
+// wavefront at a time.  The point's candidates are tested 64 at a time, one per lane, and the accepted
+// ones compacted into an LDS list (for_pairs).  Then lanes are (neighbour slot, hidden unit): HP lanes
+// per neighbour (HP >= the hidden width, a power of two), 64 / HP neighbours per step.  Each lane keeps its row of W1 and
 // its column of W2 in registers, so a message costs one lane 3 + F multiply-adds for its hidden
 // unit and `out` for its share of the output; the output is summed over hidden units and
 // neighbours by one wave reduction per point.  No edge, message or activation is stored.
@@ -36,10 +37,89 @@ constexpr int kBlock = 256;
 constexpr int kMaxBlocks = 1024;                       // persistent grid cap
 constexpr int kMaxWaves = kMaxBlocks * (kBlock / kWave);
 
-__device__ __forceinline__ float wave_sum(float v) {
+// Sums over the wavefront of N values (N a power of two up to 64): at each of the first log2 N steps a lane
+// keeps one half of its values and hands over the other, so N values take N - 1 + 6 - log2 N shuffles, not
+// 6 N.  Lane l ends with the sum of value l / (64 / N) (in all 64 / N lanes of that value).
+template <int N>
+__device__ __forceinline__ float wave_sums(float (&v)[N]) {
+    int m = kWave / 2;
 #pragma unroll
-    for (int m = 1; m < kWave; m <<= 1) v += __shfl_xor(v, m, kWave);
-    return v;
+    for (int n = N / 2; n >= 1; n /= 2, m /= 2) {
+        const bool up = (lane_id() & m) != 0;
+#pragma unroll
+        for (int k = 0; k < n; ++k) {
+            const float give = up ? v[k] : v[k + n], own = up ? v[k + n] : v[k];
+            v[k] = own + __shfl_xor(give, m, kWave);
+        }
+    }
+    float r = v[0];
+#pragma unroll
+    for (; m >= 1; m /= 2) r += __shfl_xor(r, m, kWave);
+    return r;
+}
+
+constexpr int kPairs = 64;   // accepted pairs between two passes
+
+// The accepted pairs of the point with record s, as entries (p_j - p_i, point id j) of `list`, at most kPairs at
+// a time: pass(count).  The candidates (9 runs of the cell order, laid end to end) are decoded by comparing the
+// position with the runs' first positions.  (The previous form tested the 64 / HP candidates of a step, two at
+// hidden width 32, each step waiting for its records: 75 us forward and 140 us backward for 35,947 surface
+// points, 8 features, hidden width 32; FWDNOTE and BWDNOTE us now.)
+template <class Pass>
+__device__ __forceinline__ int for_pairs(const Params &p, const int64_t *__restrict__ start,
+                                         const float4 *__restrict__ rec, int64_t s, float4 pi, float r2,
+                                         float4 *__restrict__ list, Pass &&pass) {
+    const int lane = lane_id();
+    const int cx = radius::cell_axis(p, 0, pi.x), cy = radius::cell_axis(p, 1, pi.y), cz = radius::cell_axis(p, 2, pi.z);
+    const int x0 = cx > 0 ? cx - 1 : 0, x1 = cx + 1 < p.dim[0] ? cx + 1 : p.dim[0] - 1;
+    int32_t first = 0, len = 0;
+    if (lane < 9) {
+        const int z = cz - 1 + lane / 3, y = cy - 1 + lane % 3;
+        if (z >= 0 && z < p.dim[2] && y >= 0 && y < p.dim[1]) {
+            const int64_t rowc = (static_cast<int64_t>(z) * p.dim[1] + y) * p.dim[0];
+            first = static_cast<int32_t>(start[rowc + x0]);
+            len = static_cast<int32_t>(start[rowc + x1 + 1]) - first;
+        }
+    }
+    int32_t at[9], off[9], total = 0;   // first position of run k, record of a position less the position
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+        at[k] = total;
+        off[k] = __builtin_amdgcn_readlane(first, k) - total;
+        total += __builtin_amdgcn_readlane(len, k);
+    }
+    int cnt = 0, deg = 0;
+    for (int32_t c0 = 0; c0 < total; c0 += kWave) {
+        const int32_t q = c0 + lane;
+        int32_t o = off[0];
+#pragma unroll
+        for (int k = 1; k < 9; ++k) o = q >= at[k] ? off[k] : o;
+        const int64_t t = q < total ? q + o : s;   // past the end: the point itself, which is not accepted
+        const float4 pj = rec[t];
+        float d2;
+        const bool take = radius::accept(pi, pj, r2, d2) && t != s;
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(take);
+        const int nnew = __popcll(mask);
+        if (cnt + nnew > kPairs) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            pass(cnt);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            cnt = 0;
+        }
+        if (take) {
+            const int slot = cnt + __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
+                                                             __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0));
+            list[slot] = make_float4(pj.x - pi.x, pj.y - pi.y, pj.z - pi.z, pj.w);
+        }
+        cnt += nnew;
+        deg += nnew;
+    }
+    if (cnt > 0) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        pass(cnt);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    return deg;
 }
 
 // Sum over the lanes that hold the same hidden unit (the SL = 64 / HP neighbour slots).
@@ -56,11 +136,11 @@ int64_t param_count(const Net &net) {
 }
 
 // The lane's weights: row h of W1, b1[h], column h of W2 (zero for h >= hidden).
-template <int FP>
+template <int FP, int OP>
 struct LaneNet {
     float w1[3 + FP];
     float bh;
-    float w2[kMaxOut];
+    float w2[OP];
     __device__ __forceinline__ void load(const Net &net, int h) {
         const bool hv = h < net.hidden;
         const int D = 3 + net.feat;
@@ -68,152 +148,168 @@ struct LaneNet {
         for (int c = 0; c < 3 + FP; ++c) w1[c] = hv && c < D ? net.W1[h * D + c] : 0.0f;
         bh = hv ? net.b1[h] : 0.0f;
 #pragma unroll
-        for (int o = 0; o < kMaxOut; ++o) w2[o] = hv && o < net.out ? net.W2[o * net.hidden + h] : 0.0f;
+        for (int o = 0; o < OP; ++o) w2[o] = hv && o < net.out ? net.W2[o * net.hidden + h] : 0.0f;
     }
 };
 
 template <int FP>
 __device__ __forceinline__ void load_row(const float *__restrict__ x, int64_t j, int F, float (&v)[FP]) {
     const float *r = x + j * F;
+    if (F == FP) {   // whole rows: 16-byte loads, which need only the floats' alignment
+        __builtin_memcpy(v, r, sizeof v);
+        return;
+    }
 #pragma unroll
     for (int c = 0; c < FP; ++c) v[c] = c < F ? r[c] : 0.0f;
 }
 
-template <int HP, int FP>
+template <int HP, int FP, int OP>
 __global__ __launch_bounds__(kBlock) void fwd_kernel(const Params *__restrict__ prm, const int64_t *__restrict__ start,
                                                      const float4 *__restrict__ rec, int64_t n, float r2,
                                                      const float *__restrict__ x, Net net, float *__restrict__ y) {
-    constexpr int SL = kWave / HP;
+    constexpr int SL = kWave / HP, U = FP <= 8 ? 2 : 1;   // U pairs per slot in flight
+    __shared__ float4 lists[kBlock / kWave][kPairs];
     const Params p = *prm;
+    const int wv = uniform(static_cast<int>(threadIdx.x) / kWave);
+    float4 *list = lists[wv];
     const int lane = lane_id(), slot = lane / HP, h = lane % HP;
-    LaneNet<FP> L;
+    LaneNet<FP, OP> L;
     L.load(net, h);
     const int F = net.feat, O = net.out;
     const int64_t nw = static_cast<int64_t>(gridDim.x) * (kBlock / kWave);
-    for (int64_t s = uniform(static_cast<int>(xcd_block() * (kBlock / kWave) + threadIdx.x / kWave)); s < n; s += nw) {
+    for (int64_t s = static_cast<int64_t>(xcd_block()) * (kBlock / kWave) + wv; s < n; s += nw) {
         const float4 pi = rec[s];
         const int32_t i = __float_as_int(pi.w);
-        float acc[kMaxOut] = {};
-        float cnt = 0.0f;
-        radius::for_runs(p, start, pi, [&](int64_t b, int64_t e) {
-            for (int64_t t0 = b; t0 < e; t0 += SL) {
-                const int64_t t = t0 + slot;
-                const float4 pj = rec[t < e ? t : b];
-                float d2;
-                const int32_t j = __float_as_int(pj.w);
-                if (t < e && radius::accept(pi, pj, r2, d2) && j != i) {
-#pragma clang fp contract(off)
-                    const float dx = pj.x - pi.x, dy = pj.y - pi.y, dz = pj.z - pi.z;
-                    float xj[FP];
-                    load_row<FP>(x, j, F, xj);
-                    float a = L.bh + L.w1[0] * dx + L.w1[1] * dy + L.w1[2] * dz;
+        float acc[OP] = {};
+        const int deg = for_pairs(p, start, rec, s, pi, r2, list, [&](int cnt) __attribute__((always_inline)) {
+            for (int k0 = slot; k0 < cnt; k0 += SL * U) {
+                float4 e[U];
+                float xj[U][FP];
 #pragma unroll
-                    for (int c = 0; c < FP; ++c) a += L.w1[3 + c] * xj[c];
-                    const float r = fmaxf(a, 0.0f);
+                for (int u = 0; u < U; ++u) {
+                    e[u] = list[k0 + u * SL < cnt ? k0 + u * SL : k0];
+                    load_row<FP>(x, __float_as_int(e[u].w), F, xj[u]);
+                }
 #pragma unroll
-                    for (int o = 0; o < kMaxOut; ++o) acc[o] += L.w2[o] * r;
-                    cnt += h == 0 ? 1.0f : 0.0f;
+                for (int u = 0; u < U; ++u) {
+                    float a = L.bh + L.w1[0] * e[u].x + L.w1[1] * e[u].y + L.w1[2] * e[u].z;
+#pragma unroll
+                    for (int c = 0; c < FP; ++c) a += L.w1[3 + c] * xj[u][c];
+                    const float r = k0 + u * SL < cnt ? fmaxf(a, 0.0f) : 0.0f;
+#pragma unroll
+                    for (int o = 0; o < OP; ++o) acc[o] += L.w2[o] * r;
                 }
             }
         });
-        const float deg = wave_sum(cnt);
-#pragma unroll
-        for (int o = 0; o < kMaxOut; ++o) {
-            const float v = wave_sum(acc[o]);
-            if (o < O && lane == 0) y[static_cast<int64_t>(i) * O + o] = v + deg * net.b2[o];
-        }
+        const float v = wave_sums(acc);
+        const int o = lane / (kWave / OP);
+        if (lane % (kWave / OP) == 0 && o < O)
+            y[static_cast<int64_t>(i) * O + o] = v + static_cast<float>(deg) * net.b2[o];
     }
 }
 
 // At feature width 32 the kernel is held to 168 registers (3 waves per SIMD instead of 2 at 179);
 // the 8 values this spills cost less than the third wave gains. Other widths keep their registers.
-template <int HP, int FP>
+template <int HP, int FP, int OP>
 __global__ __launch_bounds__(kBlock, FP == 32 ? 3 : 1) void bwd_kernel(const Params *__restrict__ prm, const int64_t *__restrict__ start,
                                                      const float4 *__restrict__ rec, int64_t n, float r2,
                                                      const float *__restrict__ x, Net net, const float *__restrict__ dyv,
                                                      float *__restrict__ dxo, float *__restrict__ dpo,
                                                      float *__restrict__ part, int64_t P) {
-    constexpr int SL = kWave / HP;
+    constexpr int SL = kWave / HP, U = 1;   // U pairs per slot in flight
+    __shared__ float4 lists[kBlock / kWave][kPairs];
     const Params p = *prm;
     const int lane = lane_id(), slot = lane / HP, h = lane % HP;
-    LaneNet<FP> L;
+    LaneNet<FP, OP> L;
     L.load(net, h);
     const int F = net.feat, O = net.out, H = net.hidden, D = 3 + F;
-    float gW1[3 + FP] = {}, gb1 = 0.0f, gW2[kMaxOut] = {}, gb2[kMaxOut] = {};
-    const int64_t wv = uniform(static_cast<int>(xcd_block() * (kBlock / kWave) + threadIdx.x / kWave));
+    float gW1[3 + FP] = {}, gb1 = 0.0f, gW2[OP] = {}, gb2[OP] = {};
+    const int wb = uniform(static_cast<int>(threadIdx.x) / kWave);
+    float4 *list = lists[wb];
+    const int64_t wv = static_cast<int64_t>(xcd_block()) * (kBlock / kWave) + wb;
     const int64_t nw = static_cast<int64_t>(gridDim.x) * (kBlock / kWave);
     for (int64_t s = wv; s < n; s += nw) {
         const float4 pi = rec[s];
         const int32_t i = __float_as_int(pi.w);
-        float dyk[kMaxOut];
+        float dyk[OP];
 #pragma unroll
-        for (int o = 0; o < kMaxOut; ++o) dyk[o] = o < O ? dyv[static_cast<int64_t>(i) * O + o] : 0.0f;
+        for (int o = 0; o < OP; ++o) dyk[o] = o < O ? dyv[static_cast<int64_t>(i) * O + o] : 0.0f;
         float dhk = 0.0f;   // this lane's (W2^T dy_k)[h]
 #pragma unroll
-        for (int o = 0; o < kMaxOut; ++o) dhk += L.w2[o] * dyk[o];
+        for (int o = 0; o < OP; ++o) dhk += L.w2[o] * dyk[o];
         float xi[FP];
         load_row<FP>(x, i, F, xi);
         float ck = L.bh;    // the k -> l pre-activation without its displacement part
 #pragma unroll
         for (int c = 0; c < FP; ++c) ck += L.w1[3 + c] * xi[c];
-        float S = 0.0f, T = 0.0f, cnt = 0.0f;
-        radius::for_runs(p, start, pi, [&](int64_t b, int64_t e) {
-            for (int64_t t0 = b; t0 < e; t0 += SL) {
-                const int64_t t = t0 + slot;
-                const float4 pj = rec[t < e ? t : b];
-                float d2;
-                const int32_t j = __float_as_int(pj.w);
-                if (t < e && radius::accept(pi, pj, r2, d2) && j != i) {
-#pragma clang fp contract(off)
-                    const float dx = pj.x - pi.x, dy = pj.y - pi.y, dz = pj.z - pi.z;
+        float S = 0.0f, T = 0.0f;
+        const int deg = for_pairs(p, start, rec, s, pi, r2, list, [&](int cnt) __attribute__((always_inline)) {
+            for (int k0 = slot; k0 < cnt; k0 += SL * U) {
+                float4 e[U];
+                float xj[U][FP], dyl[U][OP];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    e[u] = list[k0 + u * SL < cnt ? k0 + u * SL : k0];
+                    const int32_t j = __float_as_int(e[u].w);
+                    load_row<FP>(x, j, F, xj[u]);
+#pragma unroll
+                    for (int o = 0; o < OP; ++o) dyl[u][o] = o < O ? dyv[static_cast<int64_t>(j) * O + o] : 0.0f;
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const bool live = k0 + u * SL < cnt;
+                    const float dx = e[u].x, dy = e[u].y, dz = e[u].z;
                     const float wd = L.w1[0] * dx + L.w1[1] * dy + L.w1[2] * dz;
                     // l -> k: input [d; x_l], cotangent dy_k
-                    float xj[FP];
-                    load_row<FP>(x, j, F, xj);
                     float a = L.bh + wd;
 #pragma unroll
-                    for (int c = 0; c < FP; ++c) a += L.w1[3 + c] * xj[c];
-                    const float r = fmaxf(a, 0.0f);
+                    for (int c = 0; c < FP; ++c) a += L.w1[3 + c] * xj[u][c];
+                    const float r = live ? fmaxf(a, 0.0f) : 0.0f;
 #pragma unroll
-                    for (int o = 0; o < kMaxOut; ++o) gW2[o] += dyk[o] * r;
-                    const float da = a > 0.0f ? dhk : 0.0f;
+                    for (int o = 0; o < OP; ++o) gW2[o] += dyk[o] * r;
+                    const float da = live && a > 0.0f ? dhk : 0.0f;
                     gW1[0] += da * dx;
                     gW1[1] += da * dy;
                     gW1[2] += da * dz;
 #pragma unroll
-                    for (int c = 0; c < FP; ++c) gW1[3 + c] += da * xj[c];
+                    for (int c = 0; c < FP; ++c) gW1[3 + c] += da * xj[u][c];
                     gb1 += da;
                     T += da;
                     // k -> l: input [-d; x_k], cotangent dy_l
                     float dhl = 0.0f;
 #pragma unroll
-                    for (int o = 0; o < kMaxOut; ++o)
-                        dhl += L.w2[o] * (o < O ? dyv[static_cast<int64_t>(j) * O + o] : 0.0f);
-                    S += ck - wd > 0.0f ? dhl : 0.0f;
-                    cnt += h == 0 ? 1.0f : 0.0f;
+                    for (int o = 0; o < OP; ++o) dhl += L.w2[o] * dyl[u][o];
+                    S += live && ck - wd > 0.0f ? dhl : 0.0f;
                 }
             }
         });
         // input gradients of point i: W1^T times the lane sums of da (over hidden units and slots)
-        if (dxo)
-            for (int c = 0; c < F; ++c) {
-                float w = 0.0f;
+        constexpr int NV = FP <= 8 ? 16 : (FP <= 16 ? 32 : 64);   // 3 position and FP feature values (FP = 64: below)
+        float v[NV];
 #pragma unroll
-                for (int q = 0; q < FP; ++q) w = q == c ? L.w1[3 + q] : w;
-                const float v = wave_sum(w * S);
-                if (lane == 0) dxo[static_cast<int64_t>(i) * F + c] = v;
-            }
-        if (dpo) {
+        for (int q = 0; q < NV; ++q) v[q] = 0.0f;
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                const float v = wave_sum(L.w1[a] * (S - T));
-                if (lane == 0) dpo[static_cast<int64_t>(i) * 3 + a] = v;
-            }
+        for (int q = 0; q < 3; ++q) v[q] = L.w1[q] * (S - T);
+#pragma unroll
+        for (int q = 0; q < FP; ++q)
+            if (3 + q < NV) v[3 + q] = L.w1[3 + q] * S;
+        const float g = wave_sums(v);
+        const int q = lane / (kWave / NV);
+        if (lane % (kWave / NV) == 0) {
+            if (dpo && q < 3) dpo[static_cast<int64_t>(i) * 3 + q] = g;
+            if (dxo && q >= 3 && q < 3 + F) dxo[static_cast<int64_t>(i) * F + (q - 3)] = g;
+        }
+        if constexpr (3 + FP > NV) {   // the last features of FP = 64
+            float u[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) u[k] = NV - 3 + k < FP ? L.w1[NV + k < 3 + FP ? NV + k : 0] * S : 0.0f;
+            const float t = wave_sums(u);
+            const int f = NV - 3 + lane / (kWave / 4);
+            if (lane % (kWave / 4) == 0 && dxo && f < F) dxo[static_cast<int64_t>(i) * F + f] = t;
         }
         // every message into i carries b2: db2 += deg(i) dy_i
-        const float deg = wave_sum(cnt);
 #pragma unroll
-        for (int o = 0; o < kMaxOut; ++o) gb2[o] += deg * dyk[o];
+        for (int o = 0; o < OP; ++o) gb2[o] += static_cast<float>(deg) * dyk[o];
     }
     if (!part) return;
     // this wavefront's parameter-gradient partial: [dW1 | db1 | dW2 | db2]
@@ -228,7 +324,7 @@ __global__ __launch_bounds__(kBlock, FP == 32 ? 3 : 1) void bwd_kernel(const Par
         if (slot == 0 && h < H) pw[H * D + h] = v;
     }
 #pragma unroll
-    for (int o = 0; o < kMaxOut; ++o) {
+    for (int o = 0; o < OP; ++o) {
         const float v = slot_sum<HP>(gW2[o]);
         if (slot == 0 && h < H && o < O) pw[H * D + H + o * H + h] = v;
     }
@@ -248,7 +344,8 @@ __global__ __launch_bounds__(kWave) void reduce_groups_kernel(const float *__res
     const int64_t per = (nw + kGroups - 1) / kGroups;
     const int64_t w0 = blockIdx.y * per, w1 = w0 + per < nw ? w0 + per : nw;
     float s = 0.0f;
-    for (int64_t w = w0; w < w1; ++w) s += part[w * P + q];
+#pragma unroll 8
+    for (int64_t w = w0; w < w1; ++w) s += part[w * P + q];   // 8 loads in flight, summed in order
     grp[static_cast<int64_t>(blockIdx.y) * P + q] = s;
 }
 
@@ -257,6 +354,7 @@ __global__ __launch_bounds__(kBlock) void reduce_params_kernel(const float *__re
     const int64_t q = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
     if (q >= P) return;
     float s = 0.0f;
+#pragma unroll 16
     for (int gi = 0; gi < kGroups; ++gi) s += grp[gi * P + q];
     const int64_t D = 3 + net.feat, H = net.hidden, O = net.out;
     if (q < H * D) {
@@ -275,29 +373,29 @@ int grid_blocks(int64_t n) {
     return static_cast<int>(b < kMaxBlocks ? b : kMaxBlocks);
 }
 
-template <int HP, int FP>
+template <int HP, int FP, int OP>
 int launch_fwd(int64_t n, const Cells &cl, float r2, const float *x, const Net &net, float *y, hipStream_t stream) {
     // the forward keeps no per-wavefront partials, so its grid is as large as stays resident
     // (more wavefronts in flight hide the dependent record and row loads of each point)
-    static const int per_cu = resident_blocks(reinterpret_cast<const void *>(&fwd_kernel<HP, FP>), kBlock);
+    static const int per_cu = resident_blocks(reinterpret_cast<const void *>(&fwd_kernel<HP, FP, OP>), kBlock);
     const int64_t cap = static_cast<int64_t>(device_cus()) * per_cu;
     const int64_t need = ceil_div(n, kBlock / kWave);
     const int blocks = static_cast<int>(need < cap ? need : cap);
     prof_before(stream);
-    hipLaunchKernelGGL((fwd_kernel<HP, FP>), dim3(blocks), dim3(kBlock), 0, stream, cl.prm, cl.start, cl.rec,
+    hipLaunchKernelGGL((fwd_kernel<HP, FP, OP>), dim3(blocks), dim3(kBlock), 0, stream, cl.prm, cl.start, cl.rec,
                        n, r2, x, net, y);
     prof_after(stream);
     return check_launch("edge MLP forward");
 }
 
-template <int HP, int FP>
+template <int HP, int FP, int OP>
 int launch_bwd(int64_t n, const Cells &cl, float r2, const float *x, const Net &net, const float *dy, const Grads &g,
                float *part, float *grp, hipStream_t stream) {
     const int blocks = grid_blocks(n);
     const int64_t P = param_count(net);
     const bool params = g.dW1 || g.db1 || g.dW2 || g.db2;
     prof_before(stream);
-    hipLaunchKernelGGL((bwd_kernel<HP, FP>), dim3(blocks), dim3(kBlock), 0, stream, cl.prm, cl.start, cl.rec, n, r2,
+    hipLaunchKernelGGL((bwd_kernel<HP, FP, OP>), dim3(blocks), dim3(kBlock), 0, stream, cl.prm, cl.start, cl.rec, n, r2,
                        x, net, dy, g.dx, g.dpos, params ? part : nullptr, P);
     prof_after(stream);
     if (int rc = check_launch("edge MLP backward")) return rc;
@@ -318,13 +416,21 @@ int by_feat(int F, Fn &&fn) {
     return fn(std::integral_constant<int, 64>{});
 }
 
+template <int OP, class Fn>
+int by_hidden(const Net &net, Fn &&fn) {
+    const std::integral_constant<int, OP> op;
+    if (net.hidden <= 16)
+        return by_feat<16>(net.feat, [&](auto fp) { return fn(std::integral_constant<int, 16>{}, fp, op); });
+    if (net.hidden <= 32)
+        return by_feat<32>(net.feat, [&](auto fp) { return fn(std::integral_constant<int, 32>{}, fp, op); });
+    return by_feat<64>(net.feat, [&](auto fp) { return fn(std::integral_constant<int, 64>{}, fp, op); });
+}
+
+// Outputs padded to 4 or 8: at 3 outputs the instructions of the other five were a third of a message's.
 template <class Fn>
 int dispatch(const Net &net, Fn &&fn) {
-    if (net.hidden <= 16)
-        return by_feat<16>(net.feat, [&](auto fp) { return fn(std::integral_constant<int, 16>{}, fp); });
-    if (net.hidden <= 32)
-        return by_feat<32>(net.feat, [&](auto fp) { return fn(std::integral_constant<int, 32>{}, fp); });
-    return by_feat<64>(net.feat, [&](auto fp) { return fn(std::integral_constant<int, 64>{}, fp); });
+    if (net.out <= 4) return by_hidden<4>(net, fn);
+    return by_hidden<kMaxOut>(net, fn);
 }
 
 }  // namespace
@@ -344,8 +450,8 @@ int forward(int64_t n, const float *pos, const float *x, float radius, const Net
     Cells cl;
     if (int rc = radius::build_cells(n, pos, radius, cws, cl, stream)) return rc;
     const float r2 = radius * radius;
-    return dispatch(net, [&](auto hp, auto fp) {
-        return launch_fwd<decltype(hp)::value, decltype(fp)::value>(n, cl, r2, x, net, y, stream);
+    return dispatch(net, [&](auto hp, auto fp, auto op) {
+        return launch_fwd<decltype(hp)::value, decltype(fp)::value, decltype(op)::value>(n, cl, r2, x, net, y, stream);
     });
 }
 
@@ -358,8 +464,8 @@ int backward(int64_t n, const float *pos, const float *x, float radius, const Ne
     Cells cl;
     if (int rc = radius::build_cells(n, pos, radius, cws, cl, stream)) return rc;
     const float r2 = radius * radius;
-    return dispatch(net, [&](auto hp, auto fp) {
-        return launch_bwd<decltype(hp)::value, decltype(fp)::value>(n, cl, r2, x, net, dy, g, part, grp, stream);
+    return dispatch(net, [&](auto hp, auto fp, auto op) {
+        return launch_bwd<decltype(hp)::value, decltype(fp)::value, decltype(op)::value>(n, cl, r2, x, net, dy, g, part, grp, stream);
     });
 }
 
