@@ -40,22 +40,24 @@ constexpr int kMaxWaves = kMaxBlocks * (kBlock / kWave);
 // Sums over the wavefront of N values (N a power of two up to 64): at each of the first log2 N steps a lane
 // keeps one half of its values and hands over the other, so N values take N - 1 + 6 - log2 N shuffles, not
 // 6 N.  Lane l ends with the sum of value l / (64 / N) (in all 64 / N lanes of that value).
-template <int N>
-__device__ __forceinline__ float wave_sums(float (&v)[N]) {
-    int m = kWave / 2;
+// (Recursive, so that every index is a constant: as loops, the compiler selected among the values at run time.)
+template <int N, int M = kWave / 2>
+__device__ __forceinline__ float wave_sums(const float (&v)[N]) {
+    if constexpr (M == 0) {
+        return v[0];
+    } else if constexpr (N == 1) {
+        const float r[1] = {v[0] + __shfl_xor(v[0], M, kWave)};
+        return wave_sums<1, M / 2>(r);
+    } else {
+        const bool up = (lane_id() & M) != 0;
+        float h[N / 2];
 #pragma unroll
-    for (int n = N / 2; n >= 1; n /= 2, m /= 2) {
-        const bool up = (lane_id() & m) != 0;
-#pragma unroll
-        for (int k = 0; k < n; ++k) {
-            const float give = up ? v[k] : v[k + n], own = up ? v[k + n] : v[k];
-            v[k] = own + __shfl_xor(give, m, kWave);
+        for (int k = 0; k < N / 2; ++k) {
+            const float give = up ? v[k] : v[k + N / 2], own = up ? v[k + N / 2] : v[k];
+            h[k] = own + __shfl_xor(give, M, kWave);
         }
+        return wave_sums<N / 2, M / 2>(h);
     }
-    float r = v[0];
-#pragma unroll
-    for (; m >= 1; m /= 2) r += __shfl_xor(r, m, kWave);
-    return r;
 }
 
 constexpr int kPairs = 64;   // accepted pairs between two passes
