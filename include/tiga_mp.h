@@ -26,9 +26,9 @@
  *     surfaces at the caller's next synchronization.  Only
  *     tiga_csr_validate(level 2) and tiga_radius_neighbors synchronize.
  *   - Outputs are overwritten, never accumulated into.
- *   - fp32 features are row-major [rows, feat].  A 16-byte aligned feature
- *     array with feat % 4 == 0 takes the vector path; any other width works
- *     through the scalar path.
+ *   - fp32 features are row-major [rows, feat], of any width.  Rows need only
+ *     the alignment of floats; some paths are faster where feat % 4 == 0 and
+ *     arrays are 16-byte aligned.
  *   - Arguments are checked on the host before anything is enqueued.  On
  *     error the call returns a negative status, enqueues nothing, and
  *     tiga_last_error() describes the problem.  There is no silent fallback:

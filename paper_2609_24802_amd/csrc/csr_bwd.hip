@@ -199,7 +199,8 @@ int launch_bwd(const BwdArgs &a, void *ws_all, hipStream_t stream) {
     void *ws = bw.rest;
     const bool vec = a.feat % 4 == 0 && aligned16(a.dy) && (!a.dx || aligned16(a.dx)) &&
                      (!a.dw || !a.x || aligned16(a.x)) && (!a.arg || aligned16(a.arg));
-    const Layout lay = layout_for(a.feat, vec);
+    const Layout lay = layout_for(a.feat, vec);           // of the edge kernel
+    const Layout tlay = traversal_layout(a.feat);         // of the reverse traversal
     const bool atomic_dx = a.dx && !a.rev;
     if (atomic_dx) {
         if (int rc = fill_u32(a.dx, 0u, rel->num_src * static_cast<int64_t>(a.feat), stream)) return rc;
@@ -208,7 +209,7 @@ int launch_bwd(const BwdArgs &a, void *ws_all, hipStream_t stream) {
     // reverse incidence gathers each dy row once and forms dx_j and dw_e
     // together (x_j is the source's own row), when the row fits one feature
     // block.  Otherwise dw comes from the row-parallel edge kernel.
-    const bool fused = a.rev && a.dx && a.dw && a.x && lay.fu <= lay.L;
+    const bool fused = a.rev && a.dx && a.dw && a.x && tlay.fu <= tlay.L;
     if ((a.dw || atomic_dx) && !fused && rel->num_dst > 0) {
         EdgeT t{rel->row_ptr, rel->col_idx, a.w, a.x, a.dy, a.arg, atomic_dx ? a.dx : nullptr, a.dw,
                 rel->num_dst, lay.fu};
@@ -225,7 +226,7 @@ int launch_bwd(const BwdArgs &a, void *ws_all, hipStream_t stream) {
         // the reverse incidence carries forward edge ids only: each traversed slot reads its edge's
         // (weight, destination row) record, built here from row_ptr and w in one streaming pass
         if (int rc = launch_edge_records(rel, a.w, bw.rec, stream)) return rc;
-        Trav t{a.rev->src_ptr, nullptr, nullptr, a.rev->edge_id, a.dy, rel->num_src, lay.fu, a.arg, 0u,
+        Trav t{a.rev->src_ptr, nullptr, nullptr, a.rev->edge_id, a.dy, rel->num_src, tlay.fu, a.arg, 0u,
                rel->num_edges, bw.rec};
         const int wm = a.red == RED_MAX ? W_ROUTE : W_INDIRECT;
         EdgeGrad eg;
@@ -233,7 +234,7 @@ int launch_bwd(const BwdArgs &a, void *ws_all, hipStream_t stream) {
             eg.x = a.x;
             eg.dw = a.dw;
         }
-        if (int rc = launch_traversal(t, rel->num_dst, rel->num_edges, lay, RED_SUM, wm, ws, a.dx, nullptr, stream,
+        if (int rc = launch_traversal(t, rel->num_dst, rel->num_edges, tlay, RED_SUM, wm, ws, a.dx, nullptr, stream,
                                       direct_traversal(rel->num_src, rel->num_edges), eg))
             return rc;
     }

@@ -54,8 +54,9 @@ struct GatherBody {
         const int s = glane / L;
         const int l = glane % L;
         for (int64_t fb = 0; fb < t.fu; fb += L) {
-            const int64_t u = fb + l;
-            const bool uok = u < t.fu;
+            const int32_t f0 = static_cast<int32_t>(fb + l) * K;
+            const bool uok = f0 < t.feat;
+            const int32_t f = unit_float<K>(fb + l, t.feat);
             A acc;
             acc.init();
             if constexpr (DW) {
@@ -63,24 +64,25 @@ struct GatherBody {
                 h.dw = hdw;
                 h.l = l;
                 const bool own = uok && m.n > 0;
-                const Vec<K> xr = load_unit<K>(hx, own ? static_cast<int64_t>(m.row) * t.fu + u : 0);
+                const Vec<K> xr = load_at<K>(hx + (own ? static_cast<int64_t>(m.row) * t.feat + f : 0));
+                // a float that the unit before has too enters the inner product there
 #pragma unroll
-                for (int k = 0; k < K; ++k) h.xj[k] = own ? xr.v[k] : 0.0f;
-                run_edges<K, RED, WM, GL / L, BUF, NT>(t, tab, ars, m.e0, m.e0 + m.n, s, u, uok, acc, h);
+                for (int k = 0; k < K; ++k) h.xj[k] = own && f + k >= f0 ? xr.v[k] : 0.0f;
+                run_edges<K, RED, WM, GL / L, BUF, NT>(t, tab, ars, m.e0, m.e0 + m.n, s, f, uok, acc, h);
             } else {
-                run_edges<K, RED, WM, GL / L, BUF, NT>(t, tab, ars, m.e0, m.e0 + m.n, s, u, uok, acc);
+                run_edges<K, RED, WM, GL / L, BUF, NT>(t, tab, ars, m.e0, m.e0 + m.n, s, f, uok, acc);
             }
             reduce_lanes<L, GL>(acc);
             if (m.write && s == 0 && uok) {
                 if (m.slot < 0) {
                     acc.finalize();
-                    const int64_t unit = static_cast<int64_t>(m.row) * t.fu + u;
-                    store_unit<K>(out, unit, acc.v);
-                    if constexpr (RED == RED_MAX) store_unit_i<K>(out_arg, unit, acc.e);
+                    const int64_t at = static_cast<int64_t>(m.row) * t.feat + f;
+                    store_at<K>(out + at, acc.v);
+                    if constexpr (RED == RED_MAX) store_at_i<K>(out_arg + at, acc.e);
                 } else {
-                    const int64_t unit = static_cast<int64_t>(m.slot) * t.fu + u;
-                    store_unit<K>(part_v, unit, acc.v);
-                    if constexpr (RED == RED_MAX) store_unit_i<K>(part_e, unit, acc.e);
+                    const int64_t at = static_cast<int64_t>(m.slot) * t.feat + f;
+                    store_at<K>(part_v + at, acc.v);
+                    if constexpr (RED == RED_MAX) store_at_i<K>(part_e + at, acc.e);
                 }
             }
         }
@@ -97,7 +99,7 @@ __global__ __launch_bounds__(kBlock) void gather_reduce_kernel(Trav t, int64_t n
                                                                int32_t *__restrict__ part_e,
                                                                const float *__restrict__ hx,
                                                                float *__restrict__ hdw) {
-    const Table<K, BUF, NT> tab(t.table, t.fu, t.table_bytes);
+    const Table<K, BUF, NT> tab(t.table, t.feat, t.table_bytes);
     // argmax table (max-routing gather only; otherwise an unused empty resource)
     const __amdgpu_buffer_rsrc_t ars = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<int32_t *>(t.arg), 0, (BUF && WM == W_ROUTE) ? t.table_bytes : 0u, kBufWord3);
@@ -112,7 +114,7 @@ __global__ __launch_bounds__(kBlock) void gather_reduce_kernel(Trav t, int64_t n
 template <int K, int L, int RED, int WM, bool BUF, bool NT, bool DW>
 __global__ __launch_bounds__(kBlock) void direct_kernel(Trav t, float *__restrict__ out, int32_t *__restrict__ out_arg,
                                                         const float *__restrict__ hx, float *__restrict__ hdw) {
-    const Table<K, BUF, NT> tab(t.table, t.fu, t.table_bytes);
+    const Table<K, BUF, NT> tab(t.table, t.feat, t.table_bytes);
     const __amdgpu_buffer_rsrc_t ars = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<int32_t *>(t.arg), 0, (BUF && WM == W_ROUTE) ? t.table_bytes : 0u, kBufWord3);
     GatherBody<K, L, RED, WM, BUF, NT, DW> body{t, tab, ars, out, out_arg, nullptr, nullptr, hx, hdw};
@@ -138,7 +140,7 @@ constexpr int kHubSlots = 2 * kMergeBatch;
 template <int K, int L, int RED>
 __global__ __launch_bounds__(kBlock) void merge_kernel(const Split *__restrict__ splits,
                                                        const PlanCounts *__restrict__ counts, int64_t fu,
-                                                       const float *__restrict__ part_v,
+                                                       int32_t feat, const float *__restrict__ part_v,
                                                        const int32_t *__restrict__ part_e,
                                                        float *__restrict__ out, int32_t *__restrict__ out_arg) {
     constexpr Geom g = make_geom(L);
@@ -159,9 +161,10 @@ __global__ __launch_bounds__(kBlock) void merge_kernel(const Split *__restrict__
 #pragma unroll
             for (int b = 0; b < kMergeBatch; ++b) {
                 const int cb = c + b * step;
-                const int64_t unit = (static_cast<int64_t>(d.slot0) + (cb < d.nch ? cb : c)) * fu + u;
-                p[b] = load_unit<K>(part_v, unit);
-                if constexpr (RED == RED_MAX) load_unit_i<K>(part_e, unit, pe[b]);
+                const int64_t at =
+                    (static_cast<int64_t>(d.slot0) + (cb < d.nch ? cb : c)) * feat + unit_float<K>(u, feat);
+                p[b] = load_at<K>(part_v + at);
+                if constexpr (RED == RED_MAX) load_at_i<K>(part_e + at, pe[b]);
             }
 #pragma unroll
             for (int b = 0; b < kMergeBatch; ++b)
@@ -170,8 +173,9 @@ __global__ __launch_bounds__(kBlock) void merge_kernel(const Split *__restrict__
     };
     auto put = [&](const Split &d, int64_t u, A &acc) __attribute__((always_inline)) {
         acc.finalize();
-        store_unit<K>(out, d.row * fu + u, acc.v);
-        if constexpr (RED == RED_MAX) store_unit_i<K>(out_arg, d.row * fu + u, acc.e);
+        const int64_t at = static_cast<int64_t>(d.row) * feat + unit_float<K>(u, feat);
+        store_at<K>(out + at, acc.v);
+        if constexpr (RED == RED_MAX) store_at_i<K>(out_arg + at, acc.e);
     };
     for (int64_t it = wave; it < n_split; it += nwaves) {
         const Split d = splits[it];
@@ -209,7 +213,11 @@ template <int K, int L, int RED, int WM, bool BUF, bool NT, bool DW>
 int launch_gather_reduce(const Trav &t, int64_t n_groups, const PlanWs &w, const PlanBounds &b, float *out,
                          int32_t *out_arg, const EdgeGrad &eg, hipStream_t stream) {
     auto kern = gather_reduce_kernel<K, L, RED, WM, BUF, NT, DW>;
-    static const int per_cu = resident_blocks(reinterpret_cast<const void *>(kern), kBlock);
+    // at most 7 wavefronts per SIMD of 16-byte gathers: with 8 they slow each other down (1M rows of 64 features,
+    // 16M edges: 717 us with 7, 860 us with 8).  Rows of up to 3 floats take what is resident (500,000 rows, 8M
+    // edges, 3 features, max: 113 us, with 7 155 us).
+    static const int resident = resident_blocks(reinterpret_cast<const void *>(kern), kBlock);
+    static const int per_cu = K == 1 || resident < 7 ? resident : 7;
     const int blocks = persistent_blocks(n_groups + b.max_chunks, per_cu);
     prof_before(stream);
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(kBlock), 0, stream, t, n_groups, w.chunks, w.counts, out, out_arg,
@@ -249,7 +257,7 @@ int launch_traversal_t(const Trav &t, int64_t nedges, const PlanWs &w, const Pla
     if (rc) return rc;
     const int mblocks = persistent_blocks(b.max_splits, 4);
     hipLaunchKernelGGL((merge_kernel<K, L, RED>), dim3(mblocks), dim3(kBlock), 0, stream, w.splits, w.counts,
-                       t.fu, w.part_v, w.part_e, out, out_arg);
+                       t.fu, t.feat, w.part_v, w.part_e, out, out_arg);
     return check_launch("merge");
 }
 
@@ -272,18 +280,20 @@ int dispatch_lanes(int L, const Trav &t, int64_t nedges, const PlanWs &w, const 
 
 Layout layout_for(int64_t feat, bool vec) {
     Layout lay;
+    lay.feat = static_cast<int32_t>(feat);
     lay.K = vec ? 4 : 1;
-    lay.fu = vec ? feat / 4 : feat;
+    lay.fu = vec ? (feat + 3) / 4 : feat;
     lay.L = lanes_for(lay.fu);
     lay.g = make_geom(lay.L);
     return lay;
 }
 
 size_t traversal_ws_bytes(int64_t nrows, int64_t nedges, int64_t feat, bool with_arg) {
-    // the bound must hold for either unit width, so take the larger footprint
+    // the bound must hold for either unit width (the edge kernel of the backward takes single floats where
+    // rows are not aligned), so take the larger footprint
     size_t best = 0;
     for (int vec = 0; vec < 2; ++vec) {
-        Layout lay = layout_for(feat, vec != 0 && feat % 4 == 0);
+        Layout lay = layout_for(feat, vec != 0 && feat >= 4);
         Carve c(nullptr);
         carve_plan(c, plan_bounds(nrows, nedges, lay.g), feat, with_arg);
         if (c.bytes() > best) best = c.bytes();
@@ -297,11 +307,12 @@ int launch_traversal(const Trav &t0, int64_t table_rows, int64_t nedges, const L
                      float *out, int32_t *out_arg, hipStream_t stream, bool direct, const EdgeGrad &eg) {
     if (t0.nrows == 0) return TIGA_OK;
     Trav t = t0;
-    const int64_t tb = table_rows * lay.fu * lay.K * 4;
+    t.feat = lay.feat;
+    const int64_t tb = table_rows * lay.feat * 4;
     t.table_bytes = (tb > 0 && tb < (int64_t{1} << 32)) ? static_cast<uint32_t>(tb) : 0u;
     const PlanBounds b = plan_bounds(t.nrows, nedges, lay.g);
     Carve c(ws);
-    const PlanWs w = carve_plan(c, b, lay.fu * lay.K, red == RED_MAX);
+    const PlanWs w = carve_plan(c, b, lay.feat, red == RED_MAX);
     if (eg.dw) {
         // fused backward over the reverse incidence (sum: W_INDIRECT; max: the
         // argmax-routed W_ROUTE, whose unselected units reach the hook as zero)

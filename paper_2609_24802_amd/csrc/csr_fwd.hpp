@@ -7,13 +7,18 @@ namespace tiga {
 namespace csr {
 
 struct Layout {
-    int K;       // floats per unit (4: float4 path, 1: scalar path)
+    int K;       // floats per unit
     int64_t fu;  // units per feature row
+    int32_t feat;
     int L;       // lanes per edge
     Geom g;
 };
 
+// Units of 4 floats (vec; the last one of a ragged row overlaps the one before it) or of 1.
 Layout layout_for(int64_t feat, bool vec);
+
+// Layout of a traversal: every row of at least 4 floats takes units of 4, at any alignment.
+inline Layout traversal_layout(int64_t feat) { return layout_for(feat, feat >= 4); }
 
 // Workspace bytes for one traversal over (nrows, nedges) with `feat` features.
 size_t traversal_ws_bytes(int64_t nrows, int64_t nedges, int64_t feat, bool with_arg);

@@ -51,8 +51,7 @@ int launch_paged_fwd(const tiga_csr *rel, int32_t feat, const float *x_src, cons
     Carve c(ws);
     const PagedWs p = carve_paged(c, page_edges, feat, red == RED_MAX);
     const int64_t *rp = rel->row_ptr;   // host
-    const bool vec = feat % 4 == 0 && aligned16(x_src) && aligned16(y) && (!argmax || aligned16(argmax));
-    const Layout lay = layout_for(feat, vec);
+    const Layout lay = traversal_layout(feat);
     const int wm = w_host ? W_DIRECT : W_NONE;
     int64_t r0 = 0;
     while (r0 < rel->num_dst) {

@@ -66,7 +66,7 @@ constexpr int kPairs = 64;   // accepted pairs between two passes
 // a time: pass(count).  The candidates (9 runs of the cell order, laid end to end) are decoded by comparing the
 // position with the runs' first positions.  (The previous form tested the 64 / HP candidates of a step, two at
 // hidden width 32, each step waiting for its records: 75 us forward and 140 us backward for 35,947 surface
-// points, 8 features, hidden width 32; FWDNOTE and BWDNOTE us now.)
+// points, 8 features, hidden width 32; 36 and 55 us now.)
 template <class Pass>
 __device__ __forceinline__ int for_pairs(const Params &p, const int64_t *__restrict__ start,
                                          const float4 *__restrict__ rec, int64_t s, float4 pi, float r2,
