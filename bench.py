@@ -86,7 +86,7 @@ CSR_SOURCES = ["include/tiga_mp.h", "paper_2609_24802_amd/csrc/common.hpp", "pap
                "paper_2609_24802_amd/csrc/csr_plan.hip", "paper_2609_24802_amd/csrc/csr_bwd.hpp",
                "paper_2609_24802_amd/csrc/csr_bwd.hip", "paper_2609_24802_amd/csrc/csr_util.hip"]
 VALU_LANE_OPS_PER_S = 256 * 4 * 16 * 2.4e9  # CUs * SIMDs * lanes per cycle * clock
-VALU_INSTR_PER_PAIR = 12
+VALU_INSTR_PER_PAIR = 8  # per ordered pair: 16 for both directions, without the reciprocal root
 MFMA16_PEAK_TFLOPS = 2500.0  # dense fp16 / bf16 MFMA peak
 # edges per page of the paged CSR forward on the headline graph
 PAGE_EDGES = 1 << 26
@@ -640,9 +640,8 @@ def paths(args, torch, tb, synth):
     rr = time_steps(torch, tb, lambda: tb.tiga_mp_dense_fwd(pd, qd, g["eps"]), steps, warm)
     k = float(np.mean(rr["kernel_ms"]))
     tf = nn * (nn - 1) * 20 / (k * 1e-3) / 1e12
-    # issue floor: 12 non-transcendental VALU instructions per pair (the reciprocal square root issues
-    # alongside); a wave64 VALU instruction occupies a SIMD for 4 cycles: 1024 SIMDs * 2.4 GHz / 4 * 64 lanes.
-    # The measured kernel time sits within a few per cent of this floor, on either side (clock variation).
+    # issue floor: 16 non-transcendental VALU instructions per unordered pair (the reciprocal square root
+    # issues alongside); a wave64 VALU instruction occupies a SIMD for 4 cycles: 1024 SIMDs * 2.4 GHz / 4 * 64 lanes.
     floor_ms = nn * (nn - 1) * VALU_INSTR_PER_PAIR / VALU_LANE_OPS_PER_S * 1e3
     res["dense_65536_fwd"] = dict(ms=rr["step_ms"], gpairs_per_s=nn * (nn - 1) / rr["step_ms"] / 1e6, kernel_ms=k,
                                   tflops_20_per_pair=tf, frac_valu=tf / VALU_PEAK_TFLOPS,
@@ -674,9 +673,8 @@ def paths(args, torch, tb, synth):
         ws = tb._workspace(tb.load().tiga_mp_knn_workspace(nk), pd.device)
         rr = time_steps(torch, tb, lambda: tb.tiga_mp_knn_fwd(pd, xd, g["k"], ws=ws), steps, warm)
         k = float(np.mean(rr["kernel_ms"]))
-        # queries answered and (query, neighbour) pairs selected per second; the select kernel evaluates
-        # only the candidates its exact box tests cannot exclude (at most about 8,800 per query at
-        # 131,072 points, bounded by the scalar-load counter in the kNN profile), not all n (n - 1) pairs
+        # queries answered and (query, neighbour) pairs selected per second; the select kernel evaluates only
+        # the points of the cells around a query (about 250 at 131,072 points), not all n (n - 1) pairs
         res[f"knn_{nk}_k16_f1"] = dict(ms=rr["step_ms"], select_kernel_ms=k,
                                         queries_per_s=nk / (rr["step_ms"] * 1e-3),
                                         selected_pairs_per_s=nk * g["k"] / (rr["step_ms"] * 1e-3))
