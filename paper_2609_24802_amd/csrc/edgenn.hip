@@ -5,11 +5,15 @@
 //
 // MI355X design: a persistent grid of wavefronts walks the cell-ordered points, one point per
 // wavefront at a time.  The point's candidates are tested 64 at a time, one per lane, and the accepted
-// ones compacted into an LDS list (for_pairs).  Then lanes are (neighbour slot, hidden unit): HP lanes
-// per neighbour (HP >= the hidden width, a power of two), 64 / HP neighbours per step.  Each lane keeps its row of W1 and
-// its column of W2 in registers, so a message costs one lane 3 + F multiply-adds for its hidden
-// unit and `out` for its share of the output; the output is summed over hidden units and
-// neighbours by one wave reduction per point.  No edge, message or activation is stored.
+// ones compacted into LDS lists, one per neighbour slot (for_pairs).  Then lanes are (neighbour slot,
+// hidden unit): HP lanes per neighbour (HP >= the hidden width, a power of two), 64 / HP neighbours per
+// step.  Each lane keeps its row of W1 and its column of W2 in registers, so a message costs one lane
+// 3 + F products for its hidden unit and `out` for its share of the output; the output is summed over
+// hidden units and neighbours by one wave reduction per point.  No edge, message or activation is stored.
+//
+// Every sum has one fixed order, which depends on the hidden width alone: with few outputs and a
+// cancelling cotangent the parameter gradients amplify a change of order a hundredfold (2e-5 relative
+// between two orders of the same pairs).
 //
 // The VJP uses the symmetry of the radius relation (j in N(i) iff i in N(j)).  At point k, with
 // neighbour l, a lane recomputes its hidden unit for both directed messages:
@@ -37,40 +41,63 @@ constexpr int kBlock = 256;
 constexpr int kMaxBlocks = 1024;                       // persistent grid cap
 constexpr int kMaxWaves = kMaxBlocks * (kBlock / kWave);
 
-// Sums over the wavefront of N values (N a power of two up to 64): at each of the first log2 N steps a lane
-// keeps one half of its values and hands over the other, so N values take N - 1 + 6 - log2 N shuffles, not
-// 6 N.  Lane l ends with the sum of value l / (64 / N) (in all 64 / N lanes of that value).
+// The value of lane l ^ M: within 4 lanes an operand modifier (DPP), else a cross-lane read.
+template <int M>
+__device__ __forceinline__ float from_xor(float v) {
+    if constexpr (M == 1 || M == 2)
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), M == 1 ? 0xb1 : 0x4e, 0xf, 0xf, false));
+    else
+        return __shfl_xor(v, M, kWave);
+}
+
+// Sums of N values (a power of two) over the lanes at distances M, 2 M, ..., 32: at each of the first log2 N
+// steps a lane keeps one half of its values and hands over the other, so the values cost N - 1 + the steps
+// left over in shuffles, not N per step.  Each sum adds what a butterfly over the same distances adds, in its
+// order.  Lane l ends with the sum of value sum_index<N, M>(l).
 // (Recursive, so that every index is a constant: as loops, the compiler selected among the values at run time.)
-template <int N, int M = kWave / 2>
-__device__ __forceinline__ float wave_sums(const float (&v)[N]) {
-    if constexpr (M == 0) {
+template <int N, int M>
+__device__ __forceinline__ float exchange_sums(const float (&v)[N]) {
+    if constexpr (M == kWave) {
+        static_assert(N == 1, "more values than the lanes can hold");
         return v[0];
     } else if constexpr (N == 1) {
-        const float r[1] = {v[0] + __shfl_xor(v[0], M, kWave)};
-        return wave_sums<1, M / 2>(r);
+        const float r[1] = {v[0] + from_xor<M>(v[0])};
+        return exchange_sums<1, 2 * M>(r);
     } else {
         const bool up = (lane_id() & M) != 0;
         float h[N / 2];
 #pragma unroll
         for (int k = 0; k < N / 2; ++k) {
             const float give = up ? v[k] : v[k + N / 2], own = up ? v[k + N / 2] : v[k];
-            h[k] = own + __shfl_xor(give, M, kWave);
+            h[k] = own + from_xor<M>(give);
         }
-        return wave_sums<N / 2, M / 2>(h);
+        return exchange_sums<N / 2, 2 * M>(h);
     }
 }
 
-constexpr int kPairs = 64;   // accepted pairs between two passes
+template <int N, int M>
+__device__ __forceinline__ int sum_index(int lane) {
+    int q = 0;
+#pragma unroll
+    for (int n = N / 2, m = M; n >= 1; n /= 2, m *= 2) q += lane & m ? n : 0;
+    return q;
+}
 
-// The accepted pairs of the point with record s, as entries (p_j - p_i, point id j) of `list`, at most kPairs at
-// a time: pass(count).  The candidates (9 runs of the cell order, laid end to end) are decoded by comparing the
-// position with the runs' first positions.  (The previous form tested the 64 / HP candidates of a step, two at
-// hidden width 32, each step waiting for its records: 75 us forward and 140 us backward for 35,947 surface
-// points, 8 features, hidden width 32; 36 and 55 us now.)
-template <class Pass>
+constexpr int kPairs = 64;             // accepted pairs of a slot between two passes
+constexpr int kListRow = kPairs + 1;   // the slots' lists start on different LDS banks
+
+// The accepted pairs of the point with record s, as entries (p_j - p_i, point id j) of a list per neighbour slot,
+// at most kPairs each at a time: pass(count of this lane's slot).  The candidates are 9 runs of the cell order,
+// laid end to end, each from a multiple of SL on, and decoded by comparing the position with the runs' bounds.
+// Slot (position in its run) mod SL takes a pair, whatever became of the others: every sum over pairs then has
+// one order for all widths of the kernels, that of testing SL candidates of a run per step.  (That form, which
+// waits for the records of every step, took 75 us forward and 140 us backward for 35,947 surface points,
+// 8 features, hidden width 32; 37 and 65 us now.)
+template <int SL, class Pass>
 __device__ __forceinline__ int for_pairs(const Params &p, const int64_t *__restrict__ start,
                                          const float4 *__restrict__ rec, int64_t s, float4 pi, float r2,
                                          float4 *__restrict__ list, Pass &&pass) {
+    static_assert(SL == 1 || SL == 2 || SL == 4, "neighbour slots");
     const int lane = lane_id();
     const int cx = radius::cell_axis(p, 0, pi.x), cy = radius::cell_axis(p, 1, pi.y), cz = radius::cell_axis(p, 2, pi.z);
     const int x0 = cx > 0 ? cx - 1 : 0, x1 = cx + 1 < p.dim[0] ? cx + 1 : p.dim[0] - 1;
@@ -83,43 +110,59 @@ __device__ __forceinline__ int for_pairs(const Params &p, const int64_t *__restr
             len = static_cast<int32_t>(start[rowc + x1 + 1]) - first;
         }
     }
-    int32_t at[9], off[9], total = 0;   // first position of run k, record of a position less the position
+    // run k: first position, position past its last, record of a position less the position
+    int32_t at[9], end[9], off[9], total = 0;
 #pragma unroll
     for (int k = 0; k < 9; ++k) {
+        total = (total + SL - 1) & -SL;
         at[k] = total;
         off[k] = __builtin_amdgcn_readlane(first, k) - total;
         total += __builtin_amdgcn_readlane(len, k);
+        end[k] = total;
     }
-    int cnt = 0, deg = 0;
+    // lanes l, l + SL, ... hold the candidates of slot l
+    constexpr uint64_t kSlotLanes = SL == 1 ? ~0ull : (SL == 2 ? 0x5555555555555555ull : 0x1111111111111111ull);
+    const int to = lane % SL, slot = lane / (kWave / SL);
+    const uint64_t mine = kSlotLanes << to;
+    uint32_t cnt = 0;   // entries of each list, a byte per slot (at most kPairs, 128 before a pass)
+    int deg = 0;
+    auto count_of = [&](int k) __attribute__((always_inline)) { return static_cast<int>((cnt >> (8 * k)) & 0xffu); };
     for (int32_t c0 = 0; c0 < total; c0 += kWave) {
         const int32_t q = c0 + lane;
-        int32_t o = off[0];
+        int32_t o = off[0], e = end[0];
 #pragma unroll
-        for (int k = 1; k < 9; ++k) o = q >= at[k] ? off[k] : o;
-        const int64_t t = q < total ? q + o : s;   // past the end: the point itself, which is not accepted
+        for (int k = 1; k < 9; ++k) {
+            o = q >= at[k] ? off[k] : o;
+            e = q >= at[k] ? end[k] : e;
+        }
+        const int64_t t = q < e ? q + o : s;   // past a run's end: the point itself, which is not accepted
         const float4 pj = rec[t];
         float d2;
         const bool take = radius::accept(pi, pj, r2, d2) && t != s;
         const uint64_t mask = __builtin_amdgcn_ballot_w64(take);
-        const int nnew = __popcll(mask);
-        if (cnt + nnew > kPairs) {
+        uint32_t nnew = 0;
+#pragma unroll
+        for (int k = 0; k < SL; ++k)
+            nnew |= static_cast<uint32_t>(__popcll(mask & (kSlotLanes << k))) << (8 * k);
+        static_assert(kPairs == 64, "a byte's top bit shows a list above 64");
+        if ((cnt + nnew + 0x3f3f3f3fu) & 0x80808080u) {
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-            pass(cnt);
+            pass(count_of(slot));
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
             cnt = 0;
         }
         if (take) {
-            const int slot = cnt + __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
-                                                             __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0));
-            list[slot] = make_float4(pj.x - pi.x, pj.y - pi.y, pj.z - pi.z, pj.w);
+            const uint64_t before = mask & mine;
+            const int pos = count_of(to) +
+                           __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(before >> 32),
+                                                     __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(before), 0));
+            list[to * kListRow + pos] = make_float4(pj.x - pi.x, pj.y - pi.y, pj.z - pi.z, pj.w);
         }
         cnt += nnew;
-        deg += nnew;
+        deg += __popcll(mask);
     }
-    if (cnt > 0) {
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-        pass(cnt);
-    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    pass(count_of(slot));
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
     return deg;
 }
@@ -170,7 +213,7 @@ __global__ __launch_bounds__(kBlock) void fwd_kernel(const Params *__restrict__ 
                                                      const float4 *__restrict__ rec, int64_t n, float r2,
                                                      const float *__restrict__ x, Net net, float *__restrict__ y) {
     constexpr int SL = kWave / HP, U = FP <= 8 ? 2 : 1;   // U pairs per slot in flight
-    __shared__ float4 lists[kBlock / kWave][kPairs];
+    __shared__ float4 lists[kBlock / kWave][SL * kListRow];
     const Params p = *prm;
     const int wv = uniform(static_cast<int>(threadIdx.x) / kWave);
     float4 *list = lists[wv];
@@ -183,31 +226,59 @@ __global__ __launch_bounds__(kBlock) void fwd_kernel(const Params *__restrict__ 
         const float4 pi = rec[s];
         const int32_t i = __float_as_int(pi.w);
         float acc[OP] = {};
-        const int deg = for_pairs(p, start, rec, s, pi, r2, list, [&](int cnt) __attribute__((always_inline)) {
-            for (int k0 = slot; k0 < cnt; k0 += SL * U) {
+        const int deg = for_pairs<SL>(p, start, rec, s, pi, r2, list, [&](int cnt) __attribute__((always_inline)) {
+            for (int k0 = 0; k0 < cnt; k0 += U) {
                 float4 e[U];
                 float xj[U][FP];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    e[u] = list[k0 + u * SL < cnt ? k0 + u * SL : k0];
+                    e[u] = list[slot * kListRow + (k0 + u < cnt ? k0 + u : k0)];
                     load_row<FP>(x, __float_as_int(e[u].w), F, xj[u]);
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
+                    // products and sums rounded one by one, here and in the backward's parameter gradients: both
+                    // decide alike which hidden units are active
+#pragma clang fp contract(off)
                     float a = L.bh + L.w1[0] * e[u].x + L.w1[1] * e[u].y + L.w1[2] * e[u].z;
 #pragma unroll
                     for (int c = 0; c < FP; ++c) a += L.w1[3 + c] * xj[u][c];
-                    const float r = k0 + u * SL < cnt ? fmaxf(a, 0.0f) : 0.0f;
+                    const float r = fmaxf(a, 0.0f);
 #pragma unroll
-                    for (int o = 0; o < OP; ++o) acc[o] += L.w2[o] * r;
+                    for (int o = 0; o < OP; ++o) {
+                        const float t = acc[o] + L.w2[o] * r;
+                        acc[o] = k0 + u < cnt ? t : acc[o];
+                    }
                 }
             }
         });
-        const float v = wave_sums(acc);
-        const int o = lane / (kWave / OP);
-        if (lane % (kWave / OP) == 0 && o < O)
-            y[static_cast<int64_t>(i) * O + o] = v + static_cast<float>(deg) * net.b2[o];
+        const float v = exchange_sums<OP, 1>(acc);
+        const int o = sum_index<OP, 1>(lane);
+        if (lane < OP && o < O) y[static_cast<int64_t>(i) * O + o] = fmaf(static_cast<float>(deg), net.b2[o], v);
     }
+}
+
+// The input gradients of a point, values Q, Q + 1, ... of 3 + FP: position (W1 column times S - T), then features
+// (column times S), each summed over the lanes.  The first step adds a lane's product unrounded to that of its odd
+// neighbour, in every even lane; the others go by exchange among the even lanes, up to 32 values at a time.
+template <int FP, int Q = 0>
+__device__ __forceinline__ void put_input_grads(const float (&w1)[3 + FP], float S, float T, int64_t i, int F,
+                                                float *__restrict__ dxo, float *__restrict__ dpo) {
+    constexpr int rest = 3 + FP - Q, N = rest <= 4 ? 4 : (rest <= 16 ? 16 : 32);
+    const int lane = lane_id();
+    float v[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const float w = k < rest ? w1[k < rest ? Q + k : 0] : 0.0f, d = Q + k < 3 ? S - T : S;
+        v[k] = fmaf(w, d, from_xor<1>(w * d));
+    }
+    const float g = exchange_sums<N, 2>(v);
+    const int q = Q + sum_index<N, 2>(lane);
+    if (lane % 2 == 0 && lane < 2 * N) {
+        if (dpo && q < 3) dpo[i * 3 + q] = g;
+        if (dxo && q >= 3 && q < 3 + F) dxo[i * F + (q - 3)] = g;
+    }
+    if constexpr (rest > N) put_input_grads<FP, Q + N>(w1, S, T, i, F, dxo, dpo);
 }
 
 // At feature width 32 the kernel is held to 168 registers (3 waves per SIMD instead of 2 at 179);
@@ -218,8 +289,8 @@ __global__ __launch_bounds__(kBlock, FP == 32 ? 3 : 1) void bwd_kernel(const Par
                                                      const float *__restrict__ x, Net net, const float *__restrict__ dyv,
                                                      float *__restrict__ dxo, float *__restrict__ dpo,
                                                      float *__restrict__ part, int64_t P) {
-    constexpr int SL = kWave / HP, U = 1;   // U pairs per slot in flight
-    __shared__ float4 lists[kBlock / kWave][kPairs];
+    constexpr int SL = kWave / HP;
+    __shared__ float4 lists[kBlock / kWave][SL * kListRow];
     const Params p = *prm;
     const int lane = lane_id(), slot = lane / HP, h = lane % HP;
     LaneNet<FP, OP> L;
@@ -238,80 +309,51 @@ __global__ __launch_bounds__(kBlock, FP == 32 ? 3 : 1) void bwd_kernel(const Par
         for (int o = 0; o < OP; ++o) dyk[o] = o < O ? dyv[static_cast<int64_t>(i) * O + o] : 0.0f;
         float dhk = 0.0f;   // this lane's (W2^T dy_k)[h]
 #pragma unroll
-        for (int o = 0; o < OP; ++o) dhk += L.w2[o] * dyk[o];
+        for (int o = 0; o < OP; ++o) dhk = fmaf(L.w2[o], dyk[o], dhk);
         float xi[FP];
         load_row<FP>(x, i, F, xi);
         float ck = L.bh;    // the k -> l pre-activation without its displacement part
 #pragma unroll
-        for (int c = 0; c < FP; ++c) ck += L.w1[3 + c] * xi[c];
+        for (int c = 0; c < FP; ++c) ck = fmaf(L.w1[3 + c], xi[c], ck);
         float S = 0.0f, T = 0.0f;
-        const int deg = for_pairs(p, start, rec, s, pi, r2, list, [&](int cnt) __attribute__((always_inline)) {
-            for (int k0 = slot; k0 < cnt; k0 += SL * U) {
-                float4 e[U];
-                float xj[U][FP], dyl[U][OP];
+        const int deg = for_pairs<SL>(p, start, rec, s, pi, r2, list, [&](int cnt) __attribute__((always_inline)) {
+            for (int k0 = 0; k0 < cnt; ++k0) {
+#pragma clang fp contract(off)
+                const float4 e = list[slot * kListRow + k0];
+                const int32_t j = __float_as_int(e.w);
+                const float dx = e.x, dy = e.y, dz = e.z;
+                float xj[FP], dyl[OP];
+                load_row<FP>(x, j, F, xj);
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    e[u] = list[k0 + u * SL < cnt ? k0 + u * SL : k0];
-                    const int32_t j = __float_as_int(e[u].w);
-                    load_row<FP>(x, j, F, xj[u]);
+                for (int o = 0; o < OP; ++o) dyl[o] = o < O ? dyv[static_cast<int64_t>(j) * O + o] : 0.0f;
+                const float wd = L.w1[0] * dx + L.w1[1] * dy + L.w1[2] * dz;
+                // l -> k: input [d; x_l], cotangent dy_k
+                float a = L.bh + wd;
 #pragma unroll
-                    for (int o = 0; o < OP; ++o) dyl[u][o] = o < O ? dyv[static_cast<int64_t>(j) * O + o] : 0.0f;
-                }
+                for (int c = 0; c < FP; ++c) a += L.w1[3 + c] * xj[c];
+                const float r = fmaxf(a, 0.0f);
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const bool live = k0 + u * SL < cnt;
-                    const float dx = e[u].x, dy = e[u].y, dz = e[u].z;
-                    const float wd = L.w1[0] * dx + L.w1[1] * dy + L.w1[2] * dz;
-                    // l -> k: input [d; x_l], cotangent dy_k
-                    float a = L.bh + wd;
+                for (int o = 0; o < OP; ++o) gW2[o] += dyk[o] * r;
+                const float da = a > 0.0f ? dhk : 0.0f;
+                gW1[0] += da * dx;
+                gW1[1] += da * dy;
+                gW1[2] += da * dz;
 #pragma unroll
-                    for (int c = 0; c < FP; ++c) a += L.w1[3 + c] * xj[u][c];
-                    const float r = live ? fmaxf(a, 0.0f) : 0.0f;
+                for (int c = 0; c < FP; ++c) gW1[3 + c] += da * xj[c];
+                gb1 += da;
+                T += da;
+                // k -> l: input [-d; x_k], cotangent dy_l
+                float dhl = 0.0f;
 #pragma unroll
-                    for (int o = 0; o < OP; ++o) gW2[o] += dyk[o] * r;
-                    const float da = live && a > 0.0f ? dhk : 0.0f;
-                    gW1[0] += da * dx;
-                    gW1[1] += da * dy;
-                    gW1[2] += da * dz;
-#pragma unroll
-                    for (int c = 0; c < FP; ++c) gW1[3 + c] += da * xj[u][c];
-                    gb1 += da;
-                    T += da;
-                    // k -> l: input [-d; x_k], cotangent dy_l
-                    float dhl = 0.0f;
-#pragma unroll
-                    for (int o = 0; o < OP; ++o) dhl += L.w2[o] * dyl[u][o];
-                    S += live && ck - wd > 0.0f ? dhl : 0.0f;
-                }
+                for (int o = 0; o < OP; ++o) dhl += L.w2[o] * dyl[o];
+                S += ck - wd > 0.0f ? dhl : 0.0f;
             }
         });
         // input gradients of point i: W1^T times the lane sums of da (over hidden units and slots)
-        constexpr int NV = FP <= 8 ? 16 : (FP <= 16 ? 32 : 64);   // 3 position and FP feature values (FP = 64: below)
-        float v[NV];
-#pragma unroll
-        for (int q = 0; q < NV; ++q) v[q] = 0.0f;
-#pragma unroll
-        for (int q = 0; q < 3; ++q) v[q] = L.w1[q] * (S - T);
-#pragma unroll
-        for (int q = 0; q < FP; ++q)
-            if (3 + q < NV) v[3 + q] = L.w1[3 + q] * S;
-        const float g = wave_sums(v);
-        const int q = lane / (kWave / NV);
-        if (lane % (kWave / NV) == 0) {
-            if (dpo && q < 3) dpo[static_cast<int64_t>(i) * 3 + q] = g;
-            if (dxo && q >= 3 && q < 3 + F) dxo[static_cast<int64_t>(i) * F + (q - 3)] = g;
-        }
-        if constexpr (3 + FP > NV) {   // the last features of FP = 64
-            float u[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) u[k] = NV - 3 + k < FP ? L.w1[NV + k < 3 + FP ? NV + k : 0] * S : 0.0f;
-            const float t = wave_sums(u);
-            const int f = NV - 3 + lane / (kWave / 4);
-            if (lane % (kWave / 4) == 0 && dxo && f < F) dxo[static_cast<int64_t>(i) * F + f] = t;
-        }
+        if (dxo || dpo) put_input_grads<FP>(L.w1, S, T, i, F, dxo, dpo);
         // every message into i carries b2: db2 += deg(i) dy_i
 #pragma unroll
-        for (int o = 0; o < OP; ++o) gb2[o] += static_cast<float>(deg) * dyk[o];
+        for (int o = 0; o < OP; ++o) gb2[o] = fmaf(static_cast<float>(deg), dyk[o], gb2[o]);
     }
     if (!part) return;
     // this wavefront's parameter-gradient partial: [dW1 | db1 | dW2 | db2]
