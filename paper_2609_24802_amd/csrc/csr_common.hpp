@@ -478,11 +478,11 @@ struct Table {
 // piece is at most one chunk of edges).  Lanes past the row's end issue no
 // loads at all (their exec bit is off).
 // Per-edge side computation of a traversal, called with each gathered unit
-// (zero for lanes past the row end) before it is weighted.  The default does
-// nothing.
+// before it is weighted and with which of its floats count (not those past the
+// row end, nor unselected ones; they are zero).  The default does nothing.
 struct NoEdgeHook {
     template <int K>
-    __device__ __forceinline__ void edge(const Vec<K> &, int32_t, bool) {}
+    __device__ __forceinline__ void edge(const Vec<K> &, const bool (&)[K], int32_t, bool) {}
 };
 
 template <int K, int RED, int WM, int SL, bool BUF, bool NT, class A, class H = NoEdgeHook>
@@ -540,13 +540,14 @@ __device__ __forceinline__ void run_edges(const Trav &t, const Table<K, BUF, NT>
 #pragma unroll
         for (int r = 0; r < kUnroll; ++r) {
             const bool live = ok[r] && uok;
+            bool keep[K];
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                bool keep = live;
-                if constexpr (WM == W_ROUTE) keep = keep && sel[r][k] == ee[r];
-                xv[r].v[k] = keep ? xv[r].v[k] : 0.0f;
+                keep[k] = live;
+                if constexpr (WM == W_ROUTE) keep[k] = live && sel[r][k] == ee[r];
+                xv[r].v[k] = keep[k] ? xv[r].v[k] : 0.0f;
             }
-            hook.template edge<K>(xv[r], ee[r], ok[r]);
+            hook.template edge<K>(xv[r], keep, ee[r], ok[r]);
             acc.add(wv[r], xv[r], e0 + k0 + r * SL + s, live);
         }
     }

@@ -14,19 +14,23 @@ constexpr int64_t kDirectRows = int64_t{1} << 16;
 
 // Edge gradient of the backward, formed during the traversal of the reverse
 // incidence: dw[e] = <x_j, dy[dst(e)]> for the source row j being folded
-// (for max, only the units whose argmax is e are nonzero when they arrive).  Each lane holds one unit of x_j; the L lanes of an edge slot add
-// their parts by a fixed shuffle tree and the slot's first lane writes dw[e].
+// (for max, over the features whose argmax is e).  Each lane holds one unit of
+// x_j; the L lanes of an edge slot add their parts by a fixed shuffle tree and
+// the slot's first lane writes dw[e].  Terms that do not count (unselected
+// features, and the unit's floats before `own`, which the unit before it has
+// too) are skipped: a zero factor would make NaN of an infinite other one.
 // The row must fit one feature block (fu <= L).
 template <int K, int L>
 struct DwHook {
     float xj[K];
     float *__restrict__ dw;
     int l;
+    int own;   // first float of the unit that counts
     template <int KK>
-    __device__ __forceinline__ void edge(const Vec<KK> &g, int32_t e, bool ok) {
+    __device__ __forceinline__ void edge(const Vec<KK> &g, const bool (&keep)[KK], int32_t e, bool ok) {
         float p = 0.0f;
 #pragma unroll
-        for (int k = 0; k < K; ++k) p = fmaf(xj[k], g.v[k], p);
+        for (int k = 0; k < K; ++k) p = keep[k] && (k == K - 1 || k >= own) ? fmaf(xj[k], g.v[k], p) : p;
 #pragma unroll
         for (int m = 1; m < L; m <<= 1) p += shfl_xor_f(p, m);
         if (ok && l == 0) dw[e] = p;
@@ -65,9 +69,9 @@ struct GatherBody {
                 h.l = l;
                 const bool own = uok && m.n > 0;
                 const Vec<K> xr = load_at<K>(hx + (own ? static_cast<int64_t>(m.row) * t.feat + f : 0));
-                // a float that the unit before has too enters the inner product there
+                h.own = f0 - f;
 #pragma unroll
-                for (int k = 0; k < K; ++k) h.xj[k] = own && f + k >= f0 ? xr.v[k] : 0.0f;
+                for (int k = 0; k < K; ++k) h.xj[k] = own ? xr.v[k] : 0.0f;
                 run_edges<K, RED, WM, GL / L, BUF, NT>(t, tab, ars, m.e0, m.e0 + m.n, s, f, uok, acc, h);
             } else {
                 run_edges<K, RED, WM, GL / L, BUF, NT>(t, tab, ars, m.e0, m.e0 + m.n, s, f, uok, acc);
