@@ -276,7 +276,7 @@ struct Both {
     int R, rows;
     int64_t npad, ntile, nb, items;
     int per;
-    int64_t grid;
+    int64_t most, grid;   // blocks: bound, and how many are launched
 };
 
 Both both_for(int64_t n) {
@@ -288,8 +288,8 @@ Both both_for(int64_t n) {
     s.nb = s.npad / s.rows;
     s.items = items_before(s.nb, s.ntile, s.rows / kJ);
     // four blocks per compute unit, each the same number of items
-    const int64_t want = 4 * 256;
-    s.per = static_cast<int>(ceil_div(s.items, want));
+    s.most = 4 * static_cast<int64_t>(device_cus());
+    s.per = static_cast<int>(ceil_div(s.items, s.most));
     s.grid = ceil_div(s.items, s.per);
     return s;
 }
@@ -311,7 +311,8 @@ Ws carve(Carve &c, int64_t n, int nsplit) {
 Ws carve(Carve &c, const Both &s) {
     Ws w;
     w.pq = c.take<float4>(s.npad);
-    w.part = c.take<float>((s.grid + s.nb) * 3 * s.rows);
+    // for the most blocks: `grid` falls and rises with n, the workspace must not
+    w.part = c.take<float>((s.most + s.nb) * 3 * s.rows);
     w.part_j = c.take<float>(row_offset(s.nb, s.npad, s.rows));
     return w;
 }
@@ -347,7 +348,10 @@ size_t workspace_bytes(int64_t n) {
     Carve c(nullptr);
     if (use_both(n)) carve(c, both_for(n));
     else carve(c, n, 64);
-    return c.bytes();
+    // a workspace for n points holds every smaller problem, so above kBothMax no less than at kBothMax
+    if (n <= kBothMax) return c.bytes();
+    const size_t least = workspace_bytes(kBothMax);
+    return c.bytes() > least ? c.bytes() : least;
 }
 
 int forward(int64_t n, const float *pos, const float *q, float eps, float *y, void *ws, hipStream_t stream) {

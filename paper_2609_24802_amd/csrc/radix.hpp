@@ -65,10 +65,13 @@ inline Ws carve(Carve &c, int64_t n) {
         w.k[i] = c.take<int32_t>(n);
         w.a[i] = c.take<int32_t>(n);
     }
-    // tiles * digits: at most kDirectTiles + n / tile rows of kMaxDigits (large inputs: 256 digits)
-    const int64_t big = ceil_div(n > 0 ? n : 1, 8 * kThreads);
+    // tiles * digits: at most kDirectTiles + n / tile rows of kMaxDigits, or of 256 above kWideKeys, where it is
+    // kept at no less than at kWideKeys, so that a workspace for n keys holds every smaller sort
+    constexpr int64_t tile = 8 * kThreads;
+    const int64_t big = ceil_div(n > 0 ? n : 1, tile);
     const int64_t rows = big > kDirectTiles ? big : kDirectTiles;
-    w.counts = c.take<uint32_t>(rows * (n <= kWideKeys ? kMaxDigits : 256));
+    const int64_t wide = kWideKeys / tile * kMaxDigits;
+    w.counts = c.take<uint32_t>(n <= kWideKeys ? rows * kMaxDigits : (rows * 256 > wide ? rows * 256 : wide));
     w.totals = c.take<uint32_t>(kMaxDigits);
     return w;
 }

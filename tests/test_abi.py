@@ -173,6 +173,23 @@ def test_workspace_queries_monotone(clib):
     assert clib.tiga_mp_dense_workspace(65536) > 65536 * 16
 
 
+@pytest.mark.parametrize("query", ["transpose", "radius", "knn", "edgenn", "dense", "csr"])
+def test_workspace_for_n_holds_every_smaller_problem(clib, query):
+    from paper_2609_24802_amd import binding as b
+    size = {"transpose": lambda n: clib.tiga_csr_transpose_workspace(C.byref(_csr(1000, 1000, n))),
+            "radius": lambda n: clib.tiga_mp_radius_workspace(n, 32),
+            "knn": clib.tiga_mp_knn_workspace,
+            "edgenn": lambda n: clib.tiga_mp_edgenn_workspace(n, 8, 32, 3),
+            "dense": clib.tiga_mp_dense_workspace,
+            "csr": lambda n: clib.tiga_mp_csr_bwd_workspace(C.byref(_csr(n, n, 16 * n)), 17, b.REDUCE_MAX)}[query]
+    n = [int(1.003 ** i) for i in range(7000)]                                       # to 1.3e9
+    n += [(1 << p) + d for p in range(8, 30) for d in (-1, 0, 1, 2, 4096)]           # the bounds of the rules
+    n += [x + d for x in (7168, 12288, 16384, 40960) for d in (-1, 0, 1)]
+    bytes_ = [size(x) for x in sorted(set(n))]
+    assert min(bytes_) > 0
+    assert all(p <= q for p, q in zip(bytes_, bytes_[1:]))
+
+
 def test_attention_errors(clib):
     from paper_2609_24802_amd import binding as b
     fake = C.c_void_p(0x10000)
