@@ -413,8 +413,9 @@ __device__ __forceinline__ int gather_cells(const Curve &c, const int32_t *__res
 
 // Squared distance within which every point lies in the (2R + 1)^3 block of level-`level` cells around
 // the cell of key `key`: the nearest face beyond which cells hold points, less a relative 2e-6 that covers
-// the roundings of the fine coordinate (2^-52), of this distance and of d2 (5 of 2^-24).  FLT_MAX without
-// such a face (then the block holds every finite point); -1 where the square could underflow.
+// the roundings of d2 (5 of 2^-24), and those of the fine coordinate and of this distance (2^-52 of the
+// coordinate, which is at most 2^kBits times a distance of a cell or more).  FLT_MAX without such a face
+// (then the block holds every finite point); -1 where the square could underflow.
 __device__ __forceinline__ float block_reach2(const Curve &c, f4 at, int key, int level, int R) {
     const float p[3] = {at.x, at.y, at.z};
     const int sub = kBits - level;
@@ -714,7 +715,9 @@ __global__ __launch_bounds__(kBlock) void wide_select_kernel(const Curve *__rest
 }
 
 // Lower bound of the squared distance from a point to the points of one level-`level` cell (border cells
-// hold the points beyond them too), with the margin of block_reach2.
+// hold the points beyond them too), with the relative margin of block_reach2.  The cell's face may be as
+// near as the roundings of the coordinates on both sides of it (each some 2^-52 of its size), so the
+// distance also gives way by 2^-50 of them.
 __device__ __forceinline__ float cell_gap2(const Curve &c, f4 at, int level, int x, int y, int z) {
     const float p[3] = {at.x, at.y, at.z};
     const int cell[3] = {x, y, z}, sub = kBits - level;
@@ -722,10 +725,10 @@ __device__ __forceinline__ float cell_gap2(const Curve &c, f4 at, int level, int
     double g2 = 0.0;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const double d = static_cast<double>(p[a]) - c.lo[a];
+        const double d = static_cast<double>(p[a]) - c.lo[a], slack = (fabs(d) + h * (cell[a] + 1)) * 0x1p-50;
         double g = 0.0;
-        if (cell[a] > 0) g = fmax(g, h * cell[a] - d);
-        if (cell[a] < (c.last[a] >> sub)) g = fmax(g, d - h * (cell[a] + 1));
+        if (cell[a] > 0) g = fmax(g, h * cell[a] - d - slack);
+        if (cell[a] < (c.last[a] >> sub)) g = fmax(g, d - h * (cell[a] + 1) - slack);
         g2 += g * g;
     }
     return g2 > 1e-30 ? static_cast<float>(fmin(g2 * (1.0 - 4e-6), static_cast<double>(__FLT_MAX__))) : 0.0f;

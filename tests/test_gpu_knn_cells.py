@@ -46,3 +46,18 @@ def test_clouds(lib, kind, k):
 @pytest.mark.parametrize("k,F", [(0, 1), (5, 0), (17, 9), (31, 3)])
 def test_sizes(lib, n, k, F):
     check(lib, points("uniform", n), F, k)
+
+
+def test_neighbours_across_a_face_closer_than_the_coordinates_round(lib):
+    # A box of [-1, 1] in x: x + 1 rounds to multiples of u above the face at 0 and of u / 2 below it.  The query at
+    # 4.6 u rounds to 5 u, so the cells left of the face look 5 u away; the source at -0.26 u is 4.86 u away and must
+    # come before the one 4.95 u to the right.  3,000 points around them crowd every level of cells.
+    n, u = 20000, 2.0 ** -52
+    rng = np.random.default_rng(8)
+    pos = np.zeros((n, 3))
+    pos[:, :2] = rng.uniform(-1, 1, (n, 2))
+    pos[0, :2], pos[1, :2] = -1, 1
+    pos[100:3100, :2] = rng.uniform(2e-4, 1.9e-3, (3000, 2))
+    pos[7:10, 0] = [4.6 * u, -0.26 * u, 9.55 * u]
+    pos[7:10, 1] = 1e-3
+    check(lib, pos.astype(np.float32), 1, 1, pts=np.arange(7, 300))
