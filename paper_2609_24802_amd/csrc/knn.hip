@@ -841,7 +841,8 @@ constexpr int kBruteWaves = 4;   // queries per block
 // time in input order, with the fp32 distance and the (distance, index) key of the cell select.
 // The query's KP smallest keys are kept one per lane (lanes 0..KP-1, ascending); a step's keys
 // below the current KP-th key are found by one ballot and inserted one at a time, so the list is
-// exact whatever the order of the scan.  With a list (far_count) the queries are its records.
+// exact whatever the order of the scan.  With a list (far_count) the queries are its records, and the
+// neighbour sums are added in key order, as for the call's other queries.
 template <int KP>
 __global__ __launch_bounds__(kBruteWaves * kWave) void brute_kernel(const float *__restrict__ pos, int64_t n, int k,
                                                                     int feat, const float *__restrict__ x,
@@ -849,8 +850,9 @@ __global__ __launch_bounds__(kBruteWaves * kWave) void brute_kernel(const float 
                                                                     const SegCount *__restrict__ far_count,
                                                                     const int2 *__restrict__ far,
                                                                     const f4 *__restrict__ rec) {
-    const int lane = lane_id();
-    int64_t q = static_cast<int64_t>(blockIdx.x) * kBruteWaves + uniform(static_cast<int>(threadIdx.x) / kWave);
+    __shared__ int32_t sels[kBruteWaves][kMaxK];
+    const int lane = lane_id(), wv = uniform(static_cast<int>(threadIdx.x) / kWave);
+    int64_t q = static_cast<int64_t>(blockIdx.x) * kBruteWaves + wv;
     if (q >= n) return;
     if (far_count) {
         // at most n listed queries, one per wavefront
@@ -879,6 +881,12 @@ __global__ __launch_bounds__(kBruteWaves * kWave) void brute_kernel(const float 
     }
     const bool has = lane < k && L < kNone;
     const int32_t sel = has ? static_cast<int32_t>(static_cast<uint32_t>(L)) : -1;
+    if (far_count) {
+        if (lane < kMaxK) sels[wv][lane] = sel;
+        lds_fence();
+        put_query(sels[wv], q, k, feat, lane, kWave, x, y, nbr);
+        return;
+    }
     if (nbr && lane < k) nbr[q * k + lane] = sel;
     for (int f = 0; f < feat; ++f) {
         float v = has ? x[static_cast<int64_t>(sel) * feat + f] : 0.0f;

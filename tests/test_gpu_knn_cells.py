@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from paper_2609_24802_amd import synth
-from tests.test_gpu_knn import check, cloud
+from tests.test_gpu_knn import check, cloud, dev
 
 pytestmark = pytest.mark.gpu
 
@@ -46,6 +46,19 @@ def test_clouds(lib, kind, k):
 @pytest.mark.parametrize("k,F", [(0, 1), (5, 0), (17, 9), (31, 3)])
 def test_sizes(lib, n, k, F):
     check(lib, points("uniform", n), F, k)
+
+
+@pytest.mark.parametrize("kind", ["uniform", "cluster", "outlier"])
+@pytest.mark.parametrize("n", [7169, 12000, 17000])
+def test_sums_are_added_in_key_order(lib, kind, n):
+    # above 7,168 points, whichever scan decides a query; the clump and the outlier reach all of them
+    pos, k = points(kind, n), 32
+    x = np.random.default_rng(n).standard_normal((n, 2)).astype(np.float32)
+    y, nbr = lib.tiga_mp_knn_fwd(dev(pos), dev(x), k, want_nbr=True)
+    nbr, want = nbr.cpu().numpy(), np.zeros((n, 2), np.float32)
+    for t in range(k):
+        want = np.where(nbr[:, t:t + 1] >= 0, want + x[nbr[:, t]], want)
+    assert np.array_equal(y.cpu().numpy(), want)
 
 
 def test_neighbours_across_a_face_closer_than_the_coordinates_round(lib):
