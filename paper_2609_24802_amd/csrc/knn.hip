@@ -594,6 +594,11 @@ __global__ __launch_bounds__(kBlock, 6) void cell_select_kernel(const Curve *__r
     uint32_t over = 0;       // queries whose finest block holds more than kNear points
     int at_level = c.base;   // lane q: the level that left query q undecided
     for (int q = 0; q < nq;) {
+        if (!((fin >> q) & 1)) {   // no finite distance: nothing is selected, whatever lies around
+            if (lane < kSelRow) sels[wv][q][lane] = -1;
+            ++q;
+            continue;
+        }
         // the table's level, or a finer one whose block is small enough (starting where the query's own
         // cell holds at most a quarter of it: lane l looks at l levels below the table's)
         int level = c.base, total = -1, qe = q;
@@ -617,7 +622,9 @@ __global__ __launch_bounds__(kBlock, 6) void cell_select_kernel(const Curve *__r
         }
         uint32_t w = 0;
         if (total < 0) {
-            over |= ((1u << qe) - 1) & ~((1u << q) - 1);
+            over |= ((1u << qe) - 1) & ~((1u << q) - 1) & static_cast<uint32_t>(fin);
+            for (int u = q; u < qe; ++u)
+                if (lane < kSelRow) sels[wv][u][lane] = -1;
         } else {
             const float reach1 = block_reach2(c, me, key, level, 1);
             int32_t(*sel)[kSelRow] = sels[wv];

@@ -68,18 +68,17 @@ def test_knn_against_oracle(lib, kind, n, k, F):
 
 
 def test_knn_all_rows_16k(lib):
-    """Every row of a 16,384-point cloud: the tile skipping must never drop a neighbour."""
+    """Every row of a 16,384-point cloud."""
     g = synth.knn_inputs(16384)
     check(lib, g["pos"], 1, 16)
 
 
 def test_knn_all_rows_above_brute_force_limit(lib):
-    """Every row of a 20,000-point cloud: above 16,384 points the relation is built and the tiled
-    select runs (below, every query scans every point); both must agree with the oracle."""
+    """Every row of clouds above 16,384 points, where queries that the cells leave open are streamed."""
     g = synth.knn_inputs(20000)
     check(lib, g["pos"], 1, 16)
     check(lib, cloud("cluster", 17000, 5), 2, 9)
-    # binary-grid coordinates: many equal distances at the box-skip boundaries of tiles and runs
+    # binary-grid coordinates: many equal distances at the faces of cells
     check(lib, cloud("grid", 18000, 6), 1, 32)
 
 

@@ -1,6 +1,7 @@
 """GPU parity of the kNN paths behind the cell directory: the cell select, the wider scan of queries near
-the faces of the cloud, and the tiled select of what both leave open, at the sizes and clouds where a
-query changes from one to the next.  Neighbour lists are exact."""
+the faces of the cloud, and the scans of what both leave open (of every point up to 16,384 points, of a
+stream of cells above), at the sizes and clouds where a query changes from one to the next.  Neighbour
+lists are exact."""
 import numpy as np
 import pytest
 
@@ -30,6 +31,17 @@ def points(kind, n):
         p = rng.random((n, 3)).astype(np.float32)
         p[rng.integers(0, n, 50), rng.integers(0, 3, 50)] = rng.choice([np.nan, np.inf, -np.inf], 50)
         return p
+    if kind == "many holes":  # more of them than a block of cells may hold
+        p = rng.random((n, 3)).astype(np.float32)
+        p[: n // 8, 1] = np.nan
+        p[rng.integers(0, n, n // 50)] = np.inf
+        return p
+    if kind == "clumps":      # clumps of more points than a block may hold, and far points
+        p = rng.random((n, 3))
+        for a in range(4):
+            p[a * 2500: (a + 1) * 2500] = rng.random(3) + 1e-6 * rng.random((2500, 3))
+        p[-9:] *= 50.0
+        return p.astype(np.float32)
     if kind == "lattice":     # more than 64 equal distances at many keys
         return synth.binary_grid_points(n, 3, (98, n), span=20)
     return cloud(kind, n, 3)
@@ -40,6 +52,17 @@ def points(kind, n):
 @pytest.mark.parametrize("k", [1, 16, 32])
 def test_clouds(lib, kind, k):
     check(lib, points(kind, 7300), 1, k)
+
+
+@pytest.mark.parametrize("kind", ["uniform", "box", "outlier", "same", "far", "tiny", "holes", "lattice", "line",
+                                  "grid", "cluster", "flat", "clumps", "many holes"])
+@pytest.mark.parametrize("n,k", [(16385, 1), (16385, 16), (20001, 32)])
+def test_clouds_behind_the_streaming_scan(lib, kind, n, k):
+    # above 16,384 points the queries that the other scans leave open are streamed
+    pos = points(kind, n)
+    rng = np.random.default_rng(1)
+    pts = np.unique(np.concatenate([np.arange(64), rng.integers(0, n, 4000), np.arange(n // 3 - 40, n // 3 + 40)]))
+    check(lib, pos, 1, k, pts=pts)
 
 
 @pytest.mark.parametrize("n", [7168, 7169, 7176, 9001])
