@@ -17,19 +17,22 @@
 //    the points of the 3 x 3 x 3 cells around its own, held in registers and shared by the queries of
 //    the cell.  Every point closer than the block's nearest open face is among them, so a query with at
 //    least k candidates inside that distance is decided: those candidates (38 of 246 on average for
-//    k = 16) are compacted and ranked by counting.  Where a block holds more than 512 points the next finer
+//    k = 16) are compacted and ranked by counting.  Where a block holds more than 512 points a finer
 //    level of the curve is taken (the box is cut four standard deviations from the mean, so that far points
 //    do not use up the levels).  Otherwise the query is listed, and a second launch
 //    scans its 5 x 5 x 5 cells, then those of coarser levels, one wavefront per listed query (they sit
-//    together at the cloud's faces, so a wavefront with eight of them would end long after the rest); a
-//    block of more than 1,536 points is streamed through a list with one key per lane in a third launch.
-//    131,072 points with a third of them in a clump of 0.002: 2,183 us with the tiles, 976 us now; a normal
-//    cloud 499 and 462 us; one far outlier 9,286 and 1,161 us.
+//    together at the cloud's faces, so a wavefront with eight of them would end long after the rest); where a
+//    block holds more than 1,536 points a third launch streams cells, the nearest first, through a list of the
+//    k smallest keys so far (up to 16,384 points: every point).
+//  - Small relations (brute_kernel): a wavefront per query streams every point through such a list.
 //  Measured, 131,072 uniform points, k = 16: the previous select (tiles of 64 queries, one per lane with its
 //  keys sorted in registers, whose insertion ran for the whole wavefront whenever one lane accepted) took
-//  366 us, the cell select takes 75 us and the second launch 15 us (k = 32, whole call: 1,424 us before,
-//  174 us now).  The cell select is bound by VALU issue: about 8 tests per selected neighbour and 2
-//  instructions per pair of compacted candidates.
+//  366 us, the cell select takes 78 us and the second launch 15 us (k = 32, whole call: 1,408 us before,
+//  179 us now).  The cell select is bound by VALU issue: about 8 tests per selected neighbour and 2
+//  instructions per pair of compacted candidates.  131,072 points of unequal density, k = 16, whole calls,
+//  tiles and now: a third in a clump of 0.002 2,173 and 796 us, normal 507 and 378 us, one far outlier
+//  3,375 and 328 us, 100 copies of each position 231 and 206 us.  At k = 4, clusters whose finest cells are
+//  below the table are still slower than the tiles were (50 clusters: 258 and 317 us).
 #include "knn.hpp"
 
 #include <cmath>
@@ -44,8 +47,8 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kBits = 10;                                 // Morton bits per axis
-constexpr uint64_t kNone = 0x7f80000000000000ull;         // key (+inf, 0): above every finite key
 constexpr int kPartials = 256;                            // read by every block of the key kernel
+constexpr int kMoments = 7;
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 
@@ -59,10 +62,14 @@ struct Curve {
     int last[3];   // highest fine coordinate that holds a finite point
 };
 
-constexpr int kQueries = 8;       // queries per wavefront of the cell select
+constexpr int kQueries = 8;       // queries per wavefront of the cell select, at most
 constexpr int kNear = 512;        // candidates of the 27 cells, held in registers (8 per lane)
 constexpr int kFar = 1536;        // candidates of the 125 cells (24 per lane)
 constexpr int kMaxK = 32;
+
+// Two queries per wavefront below this many points: a wavefront's queries follow one another, each through a
+// chain of dependent loads, and with eight there are too few wavefronts to cover it.
+constexpr int64_t kFewQueries = 24000;
 
 // Undecided queries for the wider scan: kSegs lists (block b appends to list b % kSegs, so that the
 // appends do not all wait for one counter), each as long as its blocks' queries.
@@ -77,7 +84,7 @@ __host__ __device__ inline int64_t seg_size(int64_t n) {
 
 struct Ws {
     float *part;        // [kPartials][6] box partials
-    double *moments;    // [kPartials][6] sums of the finite coordinates and of their squares
+    double *moments;    // [kPartials][kMoments] sums of the finite coordinates, of their squares, of ones
     Curve *curve;
     int32_t *key, *key_sorted;
     radix::Ws sort;
@@ -97,7 +104,7 @@ int max_level(int64_t n) {
 Ws carve(Carve &c, int64_t n) {
     Ws w;
     w.part = c.take<float>(kPartials * 6);
-    w.moments = c.take<double>(kPartials * 6);
+    w.moments = c.take<double>(kPartials * kMoments);
     w.curve = c.take<Curve>(1);
     w.key = c.take<int32_t>(n);
     w.key_sorted = c.take<int32_t>(n);
@@ -108,6 +115,11 @@ Ws carve(Carve &c, int64_t n) {
     w.far = c.take<int2>(kSegs * seg_size(n));
     w.rec = c.take<f4>(n);
     return w;
+}
+
+__device__ __forceinline__ void lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
 __device__ __forceinline__ bool finite3(float a, float b, float c) {
@@ -133,15 +145,15 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
-// Box and moments of the finite points: per-block partials (min xyz, max xyz; sums, sums of squares).
+// Box and moments of the finite points: per-block partials (min xyz, max xyz; sums, sums of squares, number).
 __global__ __launch_bounds__(kBlock) void box_partial_kernel(const float *__restrict__ pos, int64_t n,
                                                              float *__restrict__ part,
                                                              double *__restrict__ moments) {
     __shared__ float red[kBlock / kWave][6];
-    __shared__ double sums[kBlock / kWave][6];
+    __shared__ double sums[kBlock / kWave][kMoments];
     float v[6] = {__builtin_inff(), __builtin_inff(), __builtin_inff(),
                   -__builtin_inff(), -__builtin_inff(), -__builtin_inff()};
-    double s[6] = {};
+    double s[kMoments] = {};
     const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < n; i += stride) {
         const float p[3] = {pos[i * 3], pos[i * 3 + 1], pos[i * 3 + 2]};
@@ -153,28 +165,28 @@ __global__ __launch_bounds__(kBlock) void box_partial_kernel(const float *__rest
             s[a] += p[a];
             s[3 + a] += static_cast<double>(p[a]) * p[a];
         }
+        s[6] += 1.0;
     }
 #pragma unroll
-    for (int a = 0; a < 6; ++a) {
-        v[a] = a < 3 ? wave_min(v[a]) : wave_max(v[a]);
-        s[a] = wave_sum(s[a]);
-    }
+    for (int a = 0; a < 6; ++a) v[a] = a < 3 ? wave_min(v[a]) : wave_max(v[a]);
+#pragma unroll
+    for (int a = 0; a < kMoments; ++a) s[a] = wave_sum(s[a]);
     const int w = threadIdx.x / kWave;
-    if (lane_id() == 0)
-        for (int a = 0; a < 6; ++a) {
-            red[w][a] = v[a];
-            sums[w][a] = s[a];
-        }
+    if (lane_id() == 0) {
+        for (int a = 0; a < 6; ++a) red[w][a] = v[a];
+        for (int a = 0; a < kMoments; ++a) sums[w][a] = s[a];
+    }
     __syncthreads();
     if (threadIdx.x < 6) {
         float r = red[0][threadIdx.x];
-        double t = sums[0][threadIdx.x];
-        for (int q = 1; q < kBlock / kWave; ++q) {
+        for (int q = 1; q < kBlock / kWave; ++q)
             r = threadIdx.x < 3 ? fminf(r, red[q][threadIdx.x]) : fmaxf(r, red[q][threadIdx.x]);
-            t += sums[q][threadIdx.x];
-        }
         part[blockIdx.x * 6 + threadIdx.x] = r;
-        moments[blockIdx.x * 6 + threadIdx.x] = t;
+    }
+    if (threadIdx.x < kMoments) {
+        double t = sums[0][threadIdx.x];
+        for (int q = 1; q < kBlock / kWave; ++q) t += sums[q][threadIdx.x];
+        moments[blockIdx.x * kMoments + threadIdx.x] = t;
     }
 }
 
@@ -208,30 +220,36 @@ __device__ __forceinline__ uint32_t fine_axis(const Curve &c, int a, float v) {
     return static_cast<uint32_t>(t < top ? t : top);
 }
 
-// Cell size for the box: `points` points per cell if the cloud were uniform, coarser where the table
-// (base <= top) or the curve's scale (the longest axis) asks for it.  The box is cut four standard
-// deviations from the mean: a few far points must not take the resolution from all others (points
-// outside the cut share its border cells).
-__device__ __forceinline__ Curve make_curve(const float (&lo)[3], const float (&hi)[3], const double (&mom)[6],
-                                            int64_t n, double points, int top) {
+// The box cut four standard deviations from the mean (each axis by a thread of its own).
+struct Cut {
+    double lo[3], hi[3];
+};
+__device__ __forceinline__ void cut_axis(Cut &c, int a, double lo, double hi, double sum, double squares, double number) {
+    const double mean = sum / number, var = squares / number - mean * mean;
+    if (var > 0.0) {
+        const double r = 4.0 * sqrt(var);
+        if (mean - r > lo) lo = mean - r;
+        if (mean + r < hi) hi = mean + r;
+    }
+    c.lo[a] = lo;
+    c.hi[a] = hi;
+}
+
+// Cell size for the cut box: `points` points per cell if the cloud were uniform, coarser where the table
+// (base <= top) or the curve's scale (the longest axis) asks for it.  A few far points must not take the
+// resolution from all others: points outside the cut share its border cells.
+__device__ __forceinline__ Curve make_curve(const Cut &cut, const double *hi, double number, double points,
+                                            int top) {
     Curve c;
     double ext[3], vol = 1.0, longest = 0.0;
     for (int a = 0; a < 3; ++a) {
-        double l = lo[a], u = hi[a];
-        const double mean = mom[a] / static_cast<double>(n);
-        const double var = mom[3 + a] / static_cast<double>(n) - mean * mean;
-        if (var > 0.0) {
-            const double cut = 4.0 * sqrt(var);
-            if (mean - cut > l) l = mean - cut;
-            if (mean + cut < u) u = mean + cut;
-        }
-        c.lo[a] = l;
-        ext[a] = u - l;
+        c.lo[a] = cut.lo[a];
+        ext[a] = cut.hi[a] - cut.lo[a];
         if (!(ext[a] > 0.0)) ext[a] = 0.0;   // no extent, or no finite point at all
         vol *= ext[a];
         longest = fmax(longest, ext[a]);
     }
-    double h = cbrt(vol * points / static_cast<double>(n));
+    double h = cbrt(vol * points / fmax(number, 1.0));
     const double finest = longest / static_cast<double>(1 << top);
     if (!(h > finest)) h = finest;
     if (!(h > 0.0)) h = 1.0;                 // coincident points
@@ -239,12 +257,14 @@ __device__ __forceinline__ Curve make_curve(const float (&lo)[3], const float (&
     while (level < top && longest >= h * static_cast<double>(1 << level)) ++level;
     c.base = level;
     c.inv_f = static_cast<double>(1 << (kBits - level)) / h;
-    for (int a = 0; a < 3; ++a) c.last[a] = static_cast<int>(fine_axis(c, a, hi[a]));
+    for (int a = 0; a < 3; ++a) c.last[a] = static_cast<int>(fine_axis(c, a, static_cast<float>(hi[a])));
     return c;
 }
 
 // Morton key of every point (non-finite points: the last key) and the sort's first histogram.  Every
-// block reduces the box partials and forms the curve for itself; block 0 stores it.
+// block reduces the box partials and forms the curve for itself; block 0 stores it.  The moments are taken
+// again without the partials that reach past the cut: a point ten thousand extents away widens the cut a
+// hundredfold (12,000 points, k = 16, one of them far: whole call 218 us without this, 106 us with it).
 template <int ITEMS>
 __global__ __launch_bounds__(radix::kThreads) void key_kernel(const float *__restrict__ pos, int64_t n,
                                                               const float *__restrict__ part,
@@ -252,43 +272,87 @@ __global__ __launch_bounds__(radix::kThreads) void key_kernel(const float *__res
                                                               double points, int top, int rb,
                                                               Curve *__restrict__ curve, int32_t *__restrict__ key,
                                                               uint32_t *__restrict__ counts) {
+    static_assert(kPartials <= radix::kThreads && 32 * (6 + kMoments) <= radix::kThreads, "threads of the reductions");
     __shared__ uint32_t hist[radix::kMaxDigits];
-    __shared__ float red[radix::kWaves][6];
-    __shared__ double sums[radix::kWaves][6];
+    __shared__ double tot[6 + kMoments], in[6 + kMoments];
+    __shared__ uint8_t out[kPartials];
+    __shared__ bool again;
+    __shared__ Cut cut;
     __shared__ Curve sc;
-    float v[6] = {__builtin_inff(), __builtin_inff(), __builtin_inff(),
-                  -__builtin_inff(), -__builtin_inff(), -__builtin_inff()};
-    double m[6] = {};
-    for (int p = threadIdx.x; p < nparts; p += radix::kThreads)
+    const int t = threadIdx.x;
+    // 32 threads per quantity (min xyz, max xyz, moments), all loads in flight
+    constexpr int kEach = kPartials / 32;
+    const int q = t / 32;
+    if (q < 6) {
+        float u[kEach];
 #pragma unroll
-        for (int a = 0; a < 6; ++a) {
-            v[a] = a < 3 ? fminf(v[a], part[p * 6 + a]) : fmaxf(v[a], part[p * 6 + a]);
-            m[a] += moments[p * 6 + a];
+        for (int j = 0; j < kEach; ++j) {
+            const int p = j * 32 + t % 32;
+            u[j] = part[(p < nparts ? p : 0) * 6 + q];
+            if (q >= 3) u[j] = -u[j];
         }
-    if (threadIdx.x < kPartials) {   // whole wavefronts
+        float r = u[0];
 #pragma unroll
-        for (int a = 0; a < 6; ++a) {
-            v[a] = a < 3 ? wave_min(v[a]) : wave_max(v[a]);
-            m[a] = wave_sum(m[a]);
-        }
-        if (lane_id() == 0)
-            for (int a = 0; a < 6; ++a) {
-                red[threadIdx.x / kWave][a] = v[a];
-                sums[threadIdx.x / kWave][a] = m[a];
-            }
+        for (int j = 1; j < kEach; ++j) r = fminf(r, u[j]);
+#pragma unroll
+        for (int m = 1; m < 32; m <<= 1) r = fminf(r, __shfl_xor(r, m, 32));
+        if (t % 32 == 0) tot[q] = q < 3 ? r : -r;
     }
+    // the moments of the partials not marked in `out` (null: of all)
+    auto sum_moments = [&](double *into, const uint8_t *out) __attribute__((always_inline)) {
+        if (q < 6 || q >= 6 + kMoments) return;   // whole halves of wavefronts
+        double u[kEach], r = 0.0;
+#pragma unroll
+        for (int j = 0; j < kEach; ++j) {
+            const int p = j * 32 + t % 32;
+            u[j] = moments[(p < nparts ? p : 0) * kMoments + (q - 6)];
+        }
+#pragma unroll
+        for (int j = 0; j < kEach; ++j) {
+            const int p = j * 32 + t % 32;
+            r += p < nparts && !(out && out[p]) ? u[j] : 0.0;
+        }
+#pragma unroll
+        for (int m = 1; m < 32; m <<= 1) r += __shfl_xor(r, m, 32);
+        if (t % 32 == 0) into[q] = r;
+    };
+    sum_moments(tot, nullptr);
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < kPartials / kWave; ++w)
-            for (int a = 0; a < 6; ++a) {
-                v[a] = a < 3 ? fminf(v[a], red[w][a]) : fmaxf(v[a], red[w][a]);
-                m[a] += sums[w][a];
-            }
-        const float lo[3] = {v[0], v[1], v[2]}, hi[3] = {v[3], v[4], v[5]};
-        sc = make_curve(lo, hi, m, n, points, top);
+    auto put_curve = [&]() __attribute__((always_inline)) {
+        sc = make_curve(cut, tot + 3, tot[12], points, top);
         if (blockIdx.x == 0) *curve = sc;
+    };
+    if (t < kWave) {
+        bool clipped = false;
+        if (t < 3) {
+            cut_axis(cut, t, tot[t], tot[3 + t], tot[6 + t], tot[9 + t], tot[12]);
+            clipped = cut.lo[t] > tot[t] || cut.hi[t] < tot[3 + t];
+        }
+        lds_fence();
+        const bool any = __any(clipped);
+        if (t == 0) {
+            again = any;
+            if (!any) put_curve();
+        }
     }
     __syncthreads();
+    if (again) {
+        if (t < nparts) {
+            bool past = false;
+            for (int a = 0; a < 3; ++a)
+                past |= part[t * 6 + a] < cut.lo[a] || part[t * 6 + 3 + a] > cut.hi[a];
+            out[t] = past;
+        }
+        __syncthreads();
+        sum_moments(in, out);
+        __syncthreads();
+        if (t < kWave) {
+            if (t < 3 && 2.0 * in[12] > tot[12]) cut_axis(cut, t, tot[t], tot[3 + t], in[6 + t], in[9 + t], in[12]);
+            lds_fence();
+            if (t == 0) put_curve();
+        }
+        __syncthreads();
+    }
     const Curve c = sc;
     radix::key_tile<ITEMS>(n, rb, key, counts, hist, [&](int64_t i) {
         const float px = pos[i * 3], py = pos[i * 3 + 1], pz = pos[i * 3 + 2];
@@ -321,92 +385,93 @@ __device__ __forceinline__ float sqdist(f4 pi, f4 pj) {
 
 // ---- cell select
 
-// 64-bit lane shift: lane t receives lane t - 1's value (lane 0 its own).
-__device__ __forceinline__ uint64_t shift_up(uint64_t v) {
-    const int src = lane_id() > 0 ? lane_id() - 1 : 0;
-    const uint32_t lo = __builtin_amdgcn_ds_bpermute(src * 4, static_cast<int>(static_cast<uint32_t>(v)));
-    const uint32_t hi = __builtin_amdgcn_ds_bpermute(src * 4, static_cast<int>(static_cast<uint32_t>(v >> 32)));
-    return (static_cast<uint64_t>(hi) << 32) | lo;
-}
-
-__device__ __forceinline__ uint64_t readlane64(uint64_t v, int l) {
-    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(v)), l);
-    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(static_cast<uint32_t>(v >> 32)), l);
-    return (static_cast<uint64_t>(hi) << 32) | lo;
-}
-
 __device__ __forceinline__ float readlane_f(float v, int l) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
 }
 
-// Insert the keys of `mask`'s lanes below `thr` into the ascending list L (one key per lane, lanes
-// 0..kp-1) one at a time: each list lane takes its left neighbour's key or the new one.  `thr` is the
-// list's last key.
-__device__ __forceinline__ void insert_lanes(uint64_t mask, uint64_t key, int kp, uint64_t &L, uint64_t &thr) {
-    const int lane = lane_id();
-    while (mask) {
-        const int b = __builtin_ctzll(mask);
-        mask &= mask - 1;
-        const uint64_t nk = readlane64(key, b);
-        if (nk >= thr) continue;   // the list moved below it meanwhile
-        const uint64_t left = shift_up(L);
-        const uint64_t up = lane == 0 ? nk : (nk < left ? left : nk);
-        L = lane < kp ? (nk < L ? up : L) : L;
-        thr = readlane64(L, kp - 1);
-    }
-}
-
 // Working set of one query: compacted candidates (distance bits, padded for 4-wide reads, and index) and
 // the selected indices in key order (-1 past the end; one slot past k shows ties at the k-th key).
+constexpr int kPickMax = 2 * kWave;
+constexpr int kSpare = 8;   // where candidates are cut down, so many more than k may stay
 struct alignas(16) Pick {
-    uint32_t d2[kWave + 4];
-    int32_t id[kWave];
+    uint32_t d2[kPickMax + 4];
+    int32_t id[kPickMax + 4];
 };
 constexpr int kSelRow = kMaxK + 1;
 
-__device__ __forceinline__ void lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
-
-// The cell of level `level` with id m: its first record, and its number of records.
-__device__ __forceinline__ void cell_range(const Curve &c, const int32_t *__restrict__ start,
-                                           const int32_t *__restrict__ sorted, int level, uint32_t m, int &s,
-                                           int &len) {
-    if (level <= c.base) {   // a run of table cells
+// The cells of level `level` with ids m[i] (i with ok[i]; the others are empty): first records, numbers of records.
+// Above the table's level a cell is a run of table cells, below it a part of one, found by binary searches for its
+// first and its last key: all of them in step, so that their dependent loads wait together.
+template <int C>
+__device__ __forceinline__ void cell_ranges(const Curve &c, const int32_t *__restrict__ start,
+                                            const int32_t *__restrict__ sorted, int level, const uint32_t (&m)[C],
+                                            const bool (&ok)[C], int (&s)[C], int (&len)[C]) {
+    if (level <= c.base) {
         const int up = 3 * (c.base - level);
-        s = start[m << up];
-        len = start[(m + 1) << up] - s;
-    } else {                 // part of one table cell
-        const uint32_t in = m >> (3 * (level - c.base));
-        const int b = start[in], n = start[in + 1] - b, shift = 3 * (kBits - level);
-        const int64_t f = radix::lower_bound(sorted + b, n, static_cast<int64_t>(m) << shift);
-        s = b + static_cast<int>(f);
-        len = static_cast<int>(radix::lower_bound(sorted + s, n - f, static_cast<int64_t>(m + 1) << shift));
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            s[i] = ok[i] ? start[m[i] << up] : 0;
+            len[i] = ok[i] ? start[(m[i] + 1) << up] - s[i] : 0;
+        }
+        return;
+    }
+    const int shift = 3 * (kBits - level);
+    int from[C], n[C], a[C], b[C], most = 0;
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+        const uint32_t in = m[i] >> (3 * (level - c.base));
+        from[i] = ok[i] ? start[in] : 0;
+        n[i] = ok[i] ? start[in + 1] - from[i] : 0;
+        a[i] = b[i] = 0;
+        most = n[i] > most ? n[i] : most;
+    }
+    for (int step = most > 0 ? 1 << (31 - __builtin_clz(most)) : 0; step > 0; step >>= 1)
+#pragma unroll
+        for (int i = 0; i < C; ++i) {
+            const int ta = a[i] + step, tb = b[i] + step;
+            const int32_t ka = ta <= n[i] ? sorted[from[i] + ta - 1] : INT32_MAX,
+                          kb = tb <= n[i] ? sorted[from[i] + tb - 1] : INT32_MAX;
+            if (ka < static_cast<int32_t>(m[i] << shift)) a[i] = ta;
+            if (kb < static_cast<int32_t>((m[i] + 1) << shift)) b[i] = tb;
+        }
+#pragma unroll
+    for (int i = 0; i < C; ++i) {
+        s[i] = from[i] + a[i];
+        len[i] = b[i] - a[i];
     }
 }
 
-// Append the candidates of the cells i0 .. i0 + 63 (this lane: i0 + lane) of the (2R + 1)^3 block of
-// level-`level` cells around cell m0 to the table of records `tab`, which holds `have` of at most `cap`;
-// returns the new number, or -1 if they exceed `cap` (the table is then unfinished).
+// The candidates of the (2R + 1)^3 block of level-`level` cells around cell m0 to the table of records `tab`;
+// returns their number, or -1 if they exceed `cap` (the table is then unfinished).
 template <int R>
 __device__ __forceinline__ int gather_cells(const Curve &c, const int32_t *__restrict__ start,
-                                            const int32_t *__restrict__ sorted, int level, uint32_t m0, int i0,
-                                            int have, int cap, int32_t *__restrict__ tab) {
-    constexpr int W = 2 * R + 1;
-    const int i = i0 + lane_id(), top = 1 << level;
-    const int x = static_cast<int>(gather3(m0)) - R + i % W, y = static_cast<int>(gather3(m0 >> 1)) - R + (i / W) % W,
-              z = static_cast<int>(gather3(m0 >> 2)) - R + i / (W * W);
-    int s = 0, len = 0;
-    if (i < W * W * W && x >= 0 && y >= 0 && z >= 0 && x < top && y < top && z < top)
-        cell_range(c, start, sorted, level, morton(x, y, z), s, len);
-    const int l = len < cap + 1 ? len : cap + 1;   // 64 of them cannot overflow the sum
-    const int incl = wave_incl_scan(l);
-    const int total = have + __builtin_amdgcn_readlane(incl, kWave - 1);
-    if (total > cap) return -1;
-    const int at = have + incl - l;
-    for (int j = 0; __any(j < len); ++j)
-        if (j < len) tab[at + j] = s + j;
+                                            const int32_t *__restrict__ sorted, int level, uint32_t m0, int cap,
+                                            int32_t *__restrict__ tab) {
+    constexpr int W = 2 * R + 1, C = (W * W * W + kWave - 1) / kWave;
+    const int lane = lane_id(), side = 1 << level;
+    const int x0 = static_cast<int>(gather3(m0)) - R, y0 = static_cast<int>(gather3(m0 >> 1)) - R,
+              z0 = static_cast<int>(gather3(m0 >> 2)) - R;
+    uint32_t m[C];
+    bool ok[C];
+    int s[C], len[C];
+#pragma unroll
+    for (int j = 0; j < C; ++j) {
+        const int i = j * kWave + lane, x = x0 + i % W, y = y0 + (i / W) % W, z = z0 + i / (W * W);
+        ok[j] = i < W * W * W && x >= 0 && y >= 0 && z >= 0 && x < side && y < side && z < side;
+        m[j] = morton(x, y, z);
+    }
+    cell_ranges<C>(c, start, sorted, level, m, ok, s, len);
+    int total = 0;
+#pragma unroll
+    for (int j = 0; j < C; ++j) {
+        const int l = len[j] < cap + 1 ? len[j] : cap + 1;   // 64 of them cannot overflow the sum
+        const int incl = wave_incl_scan(l);
+        const int at = total + incl - l;
+        total += __builtin_amdgcn_readlane(incl, kWave - 1);
+        if (total > cap) return -1;
+        for (int i = 0; __any(i < l); ++i)
+            if (i < l) tab[at + i] = s[j] + i;
+    }
     lds_fence();
     return total;
 }
@@ -435,49 +500,13 @@ __device__ __forceinline__ float block_reach2(const Curve &c, f4 at, int key, in
     return r2 < 1e-30 ? -1.0f : (r2 < static_cast<double>(__FLT_MAX__) ? static_cast<float>(r2) : __FLT_MAX__);
 }
 
-// Select the k smallest keys of one query from the candidates (d2[b], id[b]) of the lanes (no candidate:
-// +inf) when they are decided by those within `reach` (FLT_MAX: always), and write their indices in key
-// order to sel.  False: undecided.
-template <int B>
-__device__ __forceinline__ bool pick_query(Pick &pk, const float (&d2)[B], const int (&id)[B], float reach, int k,
-                                           int32_t *__restrict__ sel) {
+// The indices of the k smallest keys of the m <= 64 candidates in `pk`, in key order, to sel (-1 before).
+__device__ __forceinline__ void rank_picks(Pick &pk, int m, int k, int32_t *__restrict__ sel) {
     const int lane = lane_id();
-    auto within = [&](float r) __attribute__((always_inline)) {
-        int m = 0;
-#pragma unroll
-        for (int b = 0; b < B; ++b) m += __popcll(__builtin_amdgcn_ballot_w64(d2[b] <= r));
-        return m;
-    };
-    int m = within(reach);
-    // fewer than k of them while points outside the block may be as close
-    if (m < k && reach != __FLT_MAX__) return false;
-    // more than a wavefront of them: shrink the bound (bisection of its bits) to one that still holds k
-    if (m > kWave) {
-        uint32_t hi = __float_as_uint(reach), lo = hi > (3u << 23) ? hi - (3u << 23) : 0;
-        if (within(__uint_as_float(lo)) >= k) lo = 0;
-        while (m > kWave && hi - lo > 1) {
-            const uint32_t mid = lo + (hi - lo) / 2;
-            const int mm = within(__uint_as_float(mid));
-            if (mm >= k) hi = mid, m = mm;
-            else lo = mid;
-        }
-        if (m > kWave) return false;   // that many equal distances
-        reach = __uint_as_float(hi);
+    if (lane < 4) {
+        pk.d2[m + lane] = ~0u;
+        pk.id[m + lane] = INT32_MAX;
     }
-    int base = 0;
-#pragma unroll
-    for (int b = 0; b < B; ++b) {
-        const bool in = d2[b] <= reach;
-        const uint64_t mask = __builtin_amdgcn_ballot_w64(in);
-        if (in) {
-            const int at = base + __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
-                                                            __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0));
-            pk.d2[at] = __float_as_uint(d2[b]);
-            pk.id[at] = id[b];
-        }
-        base += __popcll(mask);
-    }
-    if (lane < 4) pk.d2[m + lane] = ~0u;
     lds_fence();
     const uint32_t mine = lane < m ? pk.d2[lane] : ~0u;
     const int my_id = lane < m ? pk.id[lane] : 0;
@@ -493,10 +522,85 @@ __device__ __forceinline__ bool pick_query(Pick &pk, const float (&d2)[B], const
     lds_fence();
     const int slots = m < k + 1 ? m : k + 1;
     if (__any(lane < slots && sel[lane] < 0)) {
-        for (int j = 0; j < m; ++j) rank += pk.d2[j] == mine && pk.id[j] < my_id;
+        for (int j = 0; j < m; j += 4) {
+            const i32x4 o = *reinterpret_cast<const i32x4 *>(&pk.d2[j]), i = *reinterpret_cast<const i32x4 *>(&pk.id[j]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) rank += static_cast<uint32_t>(o[u]) == mine && i[u] < my_id;
+        }
         if (lane < m && rank <= k) sel[rank] = my_id;
         lds_fence();
     }
+}
+
+// Select the k smallest keys of one query from the candidates (d2[b], id[b]) of the lanes (no candidate:
+// +inf) when they are decided by those within `reach` (FLT_MAX: always), and write their indices in key
+// order to sel.  False: undecided.
+template <int B>
+__device__ __forceinline__ bool pick_query(Pick &pk, const float (&d2)[B], const int (&id)[B], float reach, int k,
+                                           int n, int32_t *__restrict__ sel) {
+    const int lane = lane_id();
+    auto within = [&](float r) __attribute__((always_inline)) {
+        int m = 0;
+#pragma unroll
+        for (int b = 0; b < B; ++b) m += __popcll(__builtin_amdgcn_ballot_w64(d2[b] <= r));
+        return m;
+    };
+    int m = within(reach);
+    // fewer than k of them while points outside the block may be as close
+    if (m < k && reach != __FLT_MAX__) return false;
+    // more than a wavefront of them: shrink the bound (bisection of its bits) to one that still holds k
+    auto compact = [&](auto &&in) __attribute__((always_inline)) {
+        int base = 0;
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            const bool keep = in(b);
+            const uint64_t mask = __builtin_amdgcn_ballot_w64(keep);
+            if (keep) {
+                const int at = base + __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
+                                                                __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0));
+                pk.d2[at] = __float_as_uint(d2[b]);
+                pk.id[at] = id[b];
+            }
+            base += __popcll(mask);
+        }
+    };
+    bool ties = false;
+    if (m > kWave) {
+        uint32_t hi = __float_as_uint(reach), lo = hi > (3u << 23) ? hi - (3u << 23) : 0;
+        int below = within(__uint_as_float(lo));   // less than k; lo = hi = 0: none
+        if (below >= k) {
+            lo = 0;
+            below = within(0.0f);
+            if (below >= k) {
+                hi = 0;
+                m = below;
+                below = 0;
+            }
+        }
+        while (m > kWave && hi - lo > 1) {
+            const uint32_t mid = lo + (hi - lo) / 2;
+            const int mm = within(__uint_as_float(mid));
+            if (mm >= k) hi = mid, m = mm;
+            else lo = mid, below = mm;
+        }
+        reach = __uint_as_float(hi);
+        if (m > kWave) {
+            // still more, so all at the distance hi but those below it: bisect their ids
+            ties = true;
+            int from = -1, last = n;
+            while (m > k + kSpare) {
+                const int mid = from + (last - from) / 2;
+                int mm = below;
+#pragma unroll
+                for (int b = 0; b < B; ++b) mm += __popcll(__builtin_amdgcn_ballot_w64(d2[b] == reach && id[b] <= mid));
+                if (mm >= k) last = mid, m = mm;
+                else from = mid;
+            }
+            compact([&](int b) { return d2[b] < reach || (d2[b] == reach && id[b] <= last); });
+        }
+    }
+    if (!ties) compact([&](int b) { return d2[b] <= reach; });
+    rank_picks(pk, m, k, sel);
     return true;
 }
 
@@ -507,7 +611,7 @@ __device__ __forceinline__ bool pick_query(Pick &pk, const float (&d2)[B], const
 template <int B>
 __device__ __forceinline__ uint32_t pick_cell(Pick &pk, int32_t (*__restrict__ sel)[kSelRow],
                                               const f4 *__restrict__ rec, const int32_t *__restrict__ tab, int total,
-                                              int k, int q, int qe, f4 me, uint64_t fin, float reach1) {
+                                              int k, int n, int q, int qe, f4 me, uint64_t fin, float reach1) {
     const int lane = lane_id();
     f4 cand[B];
 #pragma unroll
@@ -529,7 +633,7 @@ __device__ __forceinline__ uint32_t pick_cell(Pick &pk, int32_t (*__restrict__ s
             id[b] = __float_as_int(cand[b].w);
             d2[b] = id[b] == qid ? __builtin_inff() : v;   // the query itself
         }
-        if (!pick_query<B>(pk, d2, id, readlane_f(reach1, q), k, sel[q])) left |= 1u << q;
+        if (!pick_query<B>(pk, d2, id, readlane_f(reach1, q), k, n, sel[q])) left |= 1u << q;
     }
     return left;
 }
@@ -551,6 +655,89 @@ __device__ __forceinline__ void put_query(const int32_t *__restrict__ sel, int64
     }
 }
 
+// The k smallest keys of a stream of candidates: those no farther than `bound` are appended to the list in
+// `pk`, which is cut down to about k of them, and the bound to their largest distance, whenever it holds more
+// than 64.  (With the keys sorted in registers, one per lane, every key that entered cost a chain of
+// cross-lane moves: a query beside a clump of 4,000 points, whose records come ever closer, took 130 us.)
+constexpr int kAhead = 4;   // records per lane loaded together
+struct TopK {
+    Pick &pk;
+    int k, n;   // all ids are below n
+    int cnt = 0;
+    float bound = __FLT_MAX__;
+
+    __device__ __forceinline__ void offer(float d2, int id, bool ok) {
+        const bool in = d2 <= bound && ok;
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(in);
+        if (!mask) return;
+        if (in) {
+            const int at = cnt + __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
+                                                           __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0));
+            pk.d2[at] = __float_as_uint(d2);
+            pk.id[at] = id;
+        }
+        cnt += __popcll(mask);
+        if (cnt > kWave) shrink(k + kSpare);
+    }
+
+    // Drop the farthest, down to between k and `most` >= k candidates (all of them stay where they are fewer).
+    // With most = k the bound ends as the k-th distance.
+    __device__ __forceinline__ void shrink(int most) {
+        if (cnt <= most) return;
+        const int lane = lane_id();
+        lds_fence();
+        const uint32_t v0 = lane < cnt ? pk.d2[lane] : ~0u, v1 = lane + kWave < cnt ? pk.d2[lane + kWave] : ~0u;
+        const int i0 = pk.id[lane], i1 = pk.id[lane + kWave];
+        auto within = [&](uint32_t b) __attribute__((always_inline)) {
+            return __popcll(__builtin_amdgcn_ballot_w64(v0 <= b)) + __popcll(__builtin_amdgcn_ballot_w64(v1 <= b));
+        };
+        uint32_t hi = __float_as_uint(bound), lo = 0;
+        int m = cnt, below = within(0);   // below = within(lo) < k; lo = hi = 0: none
+        if (below >= k) {
+            hi = 0;
+            m = below;
+            below = 0;
+        }
+        while (m > most && hi - lo > 1) {
+            const uint32_t mid = lo + (hi - lo) / 2;
+            const int mm = within(mid);
+            if (mm >= k) hi = mid, m = mm;
+            else lo = mid, below = mm;
+        }
+        int from = -1, last = n;
+        while (m > most) {   // at the distance hi, those of the lowest ids
+            const int mid = from + (last - from) / 2;
+            const int mm = below + __popcll(__builtin_amdgcn_ballot_w64(v0 == hi && i0 <= mid)) +
+                           __popcll(__builtin_amdgcn_ballot_w64(v1 == hi && i1 <= mid));
+            if (mm >= k) last = mid, m = mm;
+            else from = mid;
+        }
+        const bool in0 = v0 < hi || (v0 == hi && i0 <= last), in1 = v1 < hi || (v1 == hi && i1 <= last);
+        const uint64_t m0 = __builtin_amdgcn_ballot_w64(in0), m1 = __builtin_amdgcn_ballot_w64(in1);
+        const int a0 = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m0 >> 32),
+                                                 __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m0), 0));
+        const int a1 = __popcll(m0) + __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m1 >> 32),
+                                                                __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m1), 0));
+        lds_fence();
+        if (in0) {
+            pk.d2[a0] = v0;
+            pk.id[a0] = i0;
+        }
+        if (in1) {
+            pk.d2[a1] = v1;
+            pk.id[a1] = i1;
+        }
+        lds_fence();
+        cnt = m;
+        bound = __uint_as_float(hi);
+    }
+
+    __device__ __forceinline__ void select(int32_t *__restrict__ sel) {
+        if (lane_id() < kSelRow) sel[lane_id()] = -1;
+        rank_picks(pk, cnt, k, sel);
+    }
+};
+
 // Call item(list, entry index) for this wavefront's share (every nw-th, from w on) of the listed queries.
 template <class F>
 __device__ __forceinline__ void for_listed(const SegCount *__restrict__ count, int64_t w, int64_t nw, F &&item) {
@@ -564,7 +751,8 @@ __device__ __forceinline__ void for_listed(const SegCount *__restrict__ count, i
     }
 }
 
-// Wavefront w takes the records [8 w, 8 w + 8) as queries, cell by cell.
+// Wavefront w takes the records [Q w, Q w + Q) as queries, cell by cell.
+template <int Q>
 __global__ __launch_bounds__(kBlock, 6) void cell_select_kernel(const Curve *__restrict__ curve,
                                                                 const int32_t *__restrict__ start,
                                                                 const f4 *__restrict__ rec,
@@ -577,14 +765,14 @@ __global__ __launch_bounds__(kBlock, 6) void cell_select_kernel(const Curve *__r
                                                                 int2 *__restrict__ far) {
     __shared__ Pick picks[kBlock / kWave];
     __shared__ int32_t tabs[kBlock / kWave][kNear];
-    __shared__ int32_t sels[kBlock / kWave][kQueries][kSelRow];
+    __shared__ int32_t sels[kBlock / kWave][Q][kSelRow];
     const int lane = lane_id(), wv = uniform(static_cast<int>(threadIdx.x) / kWave);
     Pick &pk = picks[wv];
     int32_t *tab = tabs[wv];
     const int64_t t = static_cast<int64_t>(xcd_block()) * (kBlock / kWave) + wv;
-    const int64_t r0 = t * kQueries;
+    const int64_t r0 = t * Q;
     if (r0 >= n) return;
-    const int nq = static_cast<int>(n - r0 < kQueries ? n - r0 : kQueries);
+    const int nq = static_cast<int>(n - r0 < Q ? n - r0 : Q);
     const Curve c = *curve;
     // lane q < nq: query q, its key, and how far the block of cells around it reaches
     const f4 me = rec[r0 + (lane < nq ? lane : 0)];
@@ -593,6 +781,7 @@ __global__ __launch_bounds__(kBlock, 6) void cell_select_kernel(const Curve *__r
     uint32_t wide = 0;       // undecided queries
     uint32_t over = 0;       // queries whose finest block holds more than kNear points
     int at_level = c.base;   // lane q: the level that left query q undecided
+    uint32_t crowded = ~0u;  // a table cell whose block is known to hold more than kNear points
     for (int q = 0; q < nq;) {
         if (!((fin >> q) & 1)) {   // no finite distance: nothing is selected, whatever lies around
             if (lane < kSelRow) sels[wv][q][lane] = -1;
@@ -609,14 +798,19 @@ __global__ __launch_bounds__(kBlock, 6) void cell_select_kernel(const Curve *__r
             // sorted: the queries of a cell are consecutive lanes
             const uint64_t same = __builtin_amdgcn_ballot_w64(lane < nq && static_cast<uint32_t>(key) >> down == cell);
             qe = kWave - __builtin_clzll(same);
-            lds_fence();
-            total = gather_cells<1>(c, start, sorted, level, cell, 0, 0, kNear, tab);
+            if (level != c.base || cell != crowded) {
+                lds_fence();
+                total = gather_cells<1>(c, start, sorted, level, cell, kNear, tab);
+            }
             if (total >= 0 || level == kBits) break;
             if (level++ == c.base) {
+                crowded = cell;
                 const int l = c.base + lane;
-                int b, len = kNear;
-                if (lane > 0 && l <= kBits) cell_range(c, start, sorted, l, qkey >> (3 * (kBits - l)), b, len);
-                const uint64_t small = __builtin_amdgcn_ballot_w64(len <= kNear / 4);
+                const bool look[1] = {lane > 0 && l <= kBits};
+                const uint32_t own[1] = {look[0] ? qkey >> (3 * (kBits - l)) : 0};
+                int first[1], len[1];
+                cell_ranges<1>(c, start, sorted, l, own, look, first, len);
+                const uint64_t small = __builtin_amdgcn_ballot_w64(look[0] && len[0] <= kNear / 12);
                 level = small ? c.base + __builtin_ctzll(small) : kBits;
             }
         }
@@ -630,17 +824,17 @@ __global__ __launch_bounds__(kBlock, 6) void cell_select_kernel(const Curve *__r
             int32_t(*sel)[kSelRow] = sels[wv];
             switch ((total + kWave - 1) / kWave) {
                 case 0:
-                case 1: w = pick_cell<1>(pk, sel, rec, tab, total, k, q, qe, me, fin, reach1); break;
-                case 2: w = pick_cell<2>(pk, sel, rec, tab, total, k, q, qe, me, fin, reach1); break;
-                case 3: w = pick_cell<3>(pk, sel, rec, tab, total, k, q, qe, me, fin, reach1); break;
-                case 4: w = pick_cell<4>(pk, sel, rec, tab, total, k, q, qe, me, fin, reach1); break;
-                case 5: w = pick_cell<5>(pk, sel, rec, tab, total, k, q, qe, me, fin, reach1); break;
-                case 6: w = pick_cell<6>(pk, sel, rec, tab, total, k, q, qe, me, fin, reach1); break;
-                default: w = pick_cell<8>(pk, sel, rec, tab, total, k, q, qe, me, fin, reach1); break;
+                case 1: w = pick_cell<1>(pk, sel, rec, tab, total, k, static_cast<int>(n), q, qe, me, fin, reach1); break;
+                case 2: w = pick_cell<2>(pk, sel, rec, tab, total, k, static_cast<int>(n), q, qe, me, fin, reach1); break;
+                case 3: w = pick_cell<3>(pk, sel, rec, tab, total, k, static_cast<int>(n), q, qe, me, fin, reach1); break;
+                case 4: w = pick_cell<4>(pk, sel, rec, tab, total, k, static_cast<int>(n), q, qe, me, fin, reach1); break;
+                case 5: w = pick_cell<5>(pk, sel, rec, tab, total, k, static_cast<int>(n), q, qe, me, fin, reach1); break;
+                case 6: w = pick_cell<6>(pk, sel, rec, tab, total, k, static_cast<int>(n), q, qe, me, fin, reach1); break;
+                default: w = pick_cell<8>(pk, sel, rec, tab, total, k, static_cast<int>(n), q, qe, me, fin, reach1); break;
             }
         }
         wide |= w;
-        if (lane < kQueries && ((w >> lane) & 1)) at_level = level;
+        if (lane < Q && ((w >> lane) & 1)) at_level = level;
         q = qe;
     }
     auto append = [&](uint32_t mask, SegCount *count, int2 *list, int level) __attribute__((always_inline)) {
@@ -649,22 +843,23 @@ __global__ __launch_bounds__(kBlock, 6) void cell_select_kernel(const Curve *__r
         const int s = blockIdx.x % kSegs;
         if (lane == 0) at = atomicAdd(&count[s].v, static_cast<uint32_t>(__popc(mask)));
         at = uniform(at);
-        if (lane < kQueries && ((mask >> lane) & 1))
+        if (lane < Q && ((mask >> lane) & 1))
             list[seg_size(n) * s + at + __popc(mask & ((1u << lane) - 1))] =
                 make_int2(static_cast<int32_t>(r0 + lane), level);
     };
     append(wide, seg_count, seg, at_level);
     append(over, far_count, far, kBits);
     lds_fence();
-    const int q = lane / 8;
+    constexpr int PER = kWave / Q;   // lanes per query
+    const int q = lane / PER;
     const int64_t qid = __float_as_int(__shfl(me.w, q, kWave));
-    if (q < nq && !(((wide | over) >> q) & 1)) put_query(sels[wv][q], qid, k, feat, lane % 8, 8, x, y, nbr);
+    if (q < nq && !(((wide | over) >> q) & 1)) put_query(sels[wv][q], qid, k, feat, lane % PER, PER, x, y, nbr);
 }
 
 // The listed queries, one wavefront per query: the 5 x 5 x 5 cells, from the level that left the query
 // undecided to coarser ones while the block has at most kFar points, held in registers.  What stays
 // undecided is listed for the streaming scan (a list of the same segment, so that it cannot overflow).
-__global__ __launch_bounds__(kBlock) void wide_select_kernel(const Curve *__restrict__ curve,
+__global__ __launch_bounds__(kBlock, 3) void wide_select_kernel(const Curve *__restrict__ curve,
                                                              const int32_t *__restrict__ start,
                                                              const f4 *__restrict__ rec,
                                                              const int32_t *__restrict__ sorted, int64_t n, int k,
@@ -694,10 +889,10 @@ __global__ __launch_bounds__(kBlock) void wide_select_kernel(const Curve *__rest
         for (; !done && level >= 0; --level) {
             const uint32_t cell = static_cast<uint32_t>(key) >> (3 * (kBits - level));
             lds_fence();
-            int total = 0;
-            for (int i0 = 0; i0 < 125 && total >= 0; i0 += kWave)
-                total = gather_cells<2>(c, start, sorted, level, cell, i0, total, kFar, tab);
+            const int total = gather_cells<2>(c, start, sorted, level, cell, kFar, tab);
             if (total < 0) break;
+            // too few of them, the query itself included, unless there are no others
+            if (total <= k && block_reach2(c, me, key, level, 2) != __FLT_MAX__) continue;
             if (lane < kSelRow) sel[lane] = -1;
             float d2[B];
             int id[B];
@@ -709,7 +904,7 @@ __global__ __launch_bounds__(kBlock) void wide_select_kernel(const Curve *__rest
                 const float v = sqdist(me, p);
                 d2[b] = id[b] == qid ? __builtin_inff() : v;   // the query itself, or no candidate
             }
-            done = pick_query<B>(picks[wv], d2, id, block_reach2(c, me, key, level, 2), k, sel);
+            done = pick_query<B>(picks[wv], d2, id, block_reach2(c, me, key, level, 2), k, static_cast<int>(n), sel);
         }
         if (!done) {
             // a coarser block must be looked at as a whole, from the level whose reach is larger
@@ -741,31 +936,11 @@ __device__ __forceinline__ float cell_gap2(const Curve &c, f4 at, int level, int
     return g2 > 1e-30 ? static_cast<float>(fmin(g2 * (1.0 - 4e-6), static_cast<double>(__FLT_MAX__))) : 0.0f;
 }
 
-// Fold the records [b, e) into the one-key-per-lane list L (k keys, the k-th is thr), 64 per step; the
-// next step's records are loaded ahead.  Lanes past the end hold the query itself, which is never selected.
-__device__ __forceinline__ void stream_records(const f4 *__restrict__ rec, int b, int e, f4 me, int k, uint64_t &L,
-                                               uint64_t &thr) {
-    const int lane = lane_id();
-    const int qid = __float_as_int(me.w);
-    f4 nxt = b + lane < e ? rec[b + lane] : me;
-    for (int j0 = b; j0 < e; j0 += kWave) {
-        const f4 p = nxt;
-        const int jn = j0 + kWave + lane;
-        nxt = jn < e ? rec[jn] : me;
-        const float d2 = sqdist(me, p);
-        if (!__any(d2 <= __uint_as_float(static_cast<uint32_t>(thr >> 32)))) continue;
-        const int id = __float_as_int(p.w);
-        uint64_t key = (static_cast<uint64_t>(__float_as_uint(d2)) << 32) | static_cast<uint32_t>(id);
-        if (id == qid) key = ~0ull;
-        insert_lanes(__builtin_amdgcn_ballot_w64(key < thr), key, k, L, thr);
-    }
-}
-
 // The queries that the wider scan leaves undecided, one wavefront per query: the 27 cells around it from
 // the listed level to coarser ones, streamed through the list as their children (6 x 6 x 6 cells of the next
-// finer level; the finest level as it is), the query's own first, those farther than the k-th key skipped.
+// finer level; the finest level as it is), the nearest first, until the next is farther than the k-th key.
 // Level 0 is the whole cloud, so every query is decided.
-__global__ __launch_bounds__(kBlock, 8) void stream_select_kernel(const Curve *__restrict__ curve,
+__global__ __launch_bounds__(kBlock, 4) void stream_select_kernel(const Curve *__restrict__ curve,
                                                                   const int32_t *__restrict__ start,
                                                                   const f4 *__restrict__ rec,
                                                                   const int32_t *__restrict__ sorted, int64_t n,
@@ -773,6 +948,7 @@ __global__ __launch_bounds__(kBlock, 8) void stream_select_kernel(const Curve *_
                                                                   float *__restrict__ y, int32_t *__restrict__ nbr,
                                                                   const SegCount *__restrict__ seg_count,
                                                                   const int2 *__restrict__ seg) {
+    __shared__ Pick picks[kBlock / kWave];
     __shared__ int32_t sels[kBlock / kWave][kSelRow];
     const int lane = lane_id(), wv = uniform(static_cast<int>(threadIdx.x) / kWave);
     int32_t *sel = sels[wv];
@@ -784,51 +960,78 @@ __global__ __launch_bounds__(kBlock, 8) void stream_select_kernel(const Curve *_
         const int r = uniform(e.x);
         const f4 me = rec[r];
         const int key = uniform(sorted[r]);
-        uint64_t L = kNone;
+        TopK top{picks[wv], k, static_cast<int>(n)};
+        const int qid = __float_as_int(me.w);
         for (int level = uniform(e.y);; --level) {
             const int cl = level < kBits ? level + 1 : kBits, W = level < kBits ? 6 : 3;
             const uint32_t m0 = static_cast<uint32_t>(key) >> (3 * (kBits - level));
-            const int scale = W / 3, top = 1 << cl;
+            const int scale = W / 3, side = 1 << cl;
             const int x0 = scale * (static_cast<int>(gather3(m0)) - 1),
                       y0 = scale * (static_cast<int>(gather3(m0 >> 1)) - 1),
                       z0 = scale * (static_cast<int>(gather3(m0 >> 2)) - 1);
-            const uint32_t own = static_cast<uint32_t>(key) >> (3 * (kBits - cl));
-            uint64_t thr = kNone;
-            L = kNone;
-            int b = 0, len = 0;
-            cell_range(c, start, sorted, cl, own, b, len);
-            stream_records(rec, uniform(b), uniform(b + len), me, k, L, thr);
-            for (int i0 = 0; i0 < W * W * W; i0 += kWave) {
-                const int at = i0 + lane;
+            top.cnt = 0;   // (the bound holds at every level)
+            // lane l: children l, l + 64, ... (first record, number of records, distance; taken: +inf)
+            constexpr int C = (6 * 6 * 6 + kWave - 1) / kWave;
+            uint32_t m[C];
+            bool ok[C];
+            int b[C], len[C];
+            float gap[C];
+#pragma unroll
+            for (int j = 0; j < C; ++j) {
+                const int at = j * kWave + lane;
                 const int cx = x0 + at % W, cy = y0 + (at / W) % W, cz = z0 + at / (W * W);
-                b = len = 0;
-                float gap = __builtin_inff();
-                if (at < W * W * W && cx >= 0 && cy >= 0 && cz >= 0 && cx < top && cy < top && cz < top) {
-                    const uint32_t m = morton(cx, cy, cz);
-                    gap = cell_gap2(c, me, cl, cx, cy, cz);
-                    if (m != own) cell_range(c, start, sorted, cl, m, b, len);
-                }
-                uint64_t todo = __builtin_amdgcn_ballot_w64(len > 0);
-                while (true) {
-                    todo &= __builtin_amdgcn_ballot_w64(gap <= __uint_as_float(static_cast<uint32_t>(thr >> 32)));
-                    if (!todo) break;
-                    const int o = __builtin_ctzll(todo);
-                    todo &= todo - 1;
-                    const int ob = __builtin_amdgcn_readlane(b, o);
-                    stream_records(rec, ob, ob + __builtin_amdgcn_readlane(len, o), me, k, L, thr);
-                }
+                ok[j] = at < W * W * W && cx >= 0 && cy >= 0 && cz >= 0 && cx < side && cy < side && cz < side;
+                m[j] = morton(cx, cy, cz);
+                gap[j] = cell_gap2(c, me, cl, cx, cy, cz);
             }
-            const float reach = block_reach2(c, me, key, level, 1);
-            // decided if the k-th key lies within reach, or the block holds every finite point
-            if (level == 0 || reach == __FLT_MAX__ ||
-                (thr < kNone && __uint_as_float(static_cast<uint32_t>(thr >> 32)) <= reach))
-                break;
+            cell_ranges<C>(c, start, sorted, cl, m, ok, b, len);
+#pragma unroll
+            for (int j = 0; j < C; ++j) gap[j] = len[j] > 0 ? gap[j] : __builtin_inff();
+            while (true) {
+                float near = gap[0];
+                int nb = b[0], nl = len[0];
+#pragma unroll
+                for (int j = 1; j < C; ++j) {
+                    const bool less = gap[j] < near;
+                    near = less ? gap[j] : near;
+                    nb = less ? b[j] : nb;
+                    nl = less ? len[j] : nl;
+                }
+                const float best = wave_min(near);
+                if (!(best <= top.bound)) break;   // (+inf: none left)
+                const int o = __builtin_ctzll(__builtin_amdgcn_ballot_w64(near == best));
+                const int ob = __builtin_amdgcn_readlane(nb, o);
+#pragma unroll
+                for (int j = 0; j < C; ++j) gap[j] = lane == o && b[j] == ob ? __builtin_inff() : gap[j];
+                const int oe = ob + __builtin_amdgcn_readlane(nl, o);
+                for (int j0 = ob; j0 < oe; j0 += kAhead * kWave) {
+                    f4 p[kAhead];
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        const int j = j0 + u * kWave + lane;
+                        p[u] = j < oe ? rec[j] : me;   // the query itself: left out
+                    }
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) {
+                        const int id = __float_as_int(p[u].w);
+                        top.offer(sqdist(me, p[u]), id, id != qid);
+                    }
+                }
+                if (top.bound == __FLT_MAX__ || top.cnt > k + 2 * kSpare) top.shrink(k + kSpare);
+            }
+            // decided if the k-th distance lies within reach, or the block holds every finite point; otherwise on
+            // to the first level whose reach covers it
+            top.shrink(k);
+            const bool some = top.cnt >= k;
+            const auto open = [&](int l) __attribute__((always_inline)) {
+                const float reach = block_reach2(c, me, key, l, 1);
+                return l > 0 && reach != __FLT_MAX__ && !(some && top.bound <= reach);
+            };
+            if (!open(level)) break;
+            while (some && level > 1 && open(level - 1)) --level;
         }
-        lds_fence();
-        if (lane < kSelRow)
-            sel[lane] = lane < k && L < kNone ? static_cast<int32_t>(static_cast<uint32_t>(L)) : -1;
-        lds_fence();
-        put_query(sel, __float_as_int(me.w), k, feat, lane, kWave, x, y, nbr);
+        top.select(sel);
+        put_query(sel, qid, k, feat, lane, kWave, x, y, nbr);
     });
 }
 
@@ -836,30 +1039,28 @@ __global__ __launch_bounds__(kBlock, 8) void stream_select_kernel(const Curve *_
 
 // At or below this many points every query scans every point and no relation is built (box, curve keys,
 // sort, index): the build's launches and the cell select's dependent chains cost more there than the
-// quadratic distance work.  Measured with the build and without it: 4,096 points 72 and 37 us, 8,192
-// points 73 and 84 us (k = 16); 8,192 points 66 and 63 us (k = 4), 81 and 109 us (k = 32).
-constexpr int64_t kBruteMax = 7168;
-// Up to this many points the queries that the wider scan leaves undecided scan every point too: a third of
-// 12,000 points in a tight clump took 250 us in all with the streaming scan and 200 us this way.
+// quadratic distance work, on clouds of unequal density above all.  Without the build and with it, k = 16:
+// 9,000 points, uniform 57 and 74 us, normal 55 and 128 us; 11,000 points, uniform 73 and 76 us; 12,000 points,
+// uniform 84 and 75 us.
+constexpr int64_t kBruteMax = 11000;
+// Up to this many points the queries that the wider scan leaves undecided scan every point too.
 constexpr int64_t kBruteFar = 16384;
-constexpr int kBruteWaves = 4;   // queries per block
+constexpr int64_t kTreeMax = 7168;   // sums of at most so many points are pairwise trees
+constexpr int kBruteWaves = 4;       // queries per block
 
 // Wavefront w of block b takes query q = kBruteWaves b + w; its lanes scan the points 64 at a
 // time in input order, with the fp32 distance and the (distance, index) key of the cell select.
-// The query's KP smallest keys are kept one per lane (lanes 0..KP-1, ascending); a step's keys
-// below the current KP-th key are found by one ballot and inserted one at a time, so the list is
-// exact whatever the order of the scan.  With a list (far_count) the queries are its records, and the
-// neighbour sums are added in key order, as for the call's other queries.
-template <int KP>
+// With a list (far_count) the queries are its records.
 __global__ __launch_bounds__(kBruteWaves * kWave) void brute_kernel(const float *__restrict__ pos, int64_t n, int k,
                                                                     int feat, const float *__restrict__ x,
                                                                     float *__restrict__ y, int32_t *__restrict__ nbr,
                                                                     const SegCount *__restrict__ far_count,
                                                                     const int2 *__restrict__ far,
                                                                     const f4 *__restrict__ rec) {
-    __shared__ int32_t sels[kBruteWaves][kMaxK];
+    __shared__ Pick picks[kBruteWaves];
+    __shared__ int32_t sels[kBruteWaves][kSelRow];
     const int lane = lane_id(), wv = uniform(static_cast<int>(threadIdx.x) / kWave);
-    int64_t q = static_cast<int64_t>(blockIdx.x) * kBruteWaves + wv;
+    int q = static_cast<int>(blockIdx.x) * kBruteWaves + wv;
     if (q >= n) return;
     if (far_count) {
         // at most n listed queries, one per wavefront
@@ -868,49 +1069,53 @@ __global__ __launch_bounds__(kBruteWaves * kWave) void brute_kernel(const float 
         if (listed < 0) return;
         q = uniform(__float_as_int(rec[listed].w));
     }
-    const f4 me = f4{pos[q * 3], pos[q * 3 + 1], pos[q * 3 + 2], 0.0f};   // uniform: scalar loads
-    uint64_t L = kNone;                                                      // lane t < KP: the t-th key
+    struct P3 {
+        float x, y, z;
+    };
+    const P3 *__restrict__ pts = reinterpret_cast<const P3 *>(pos);
+    const P3 mq = pts[q];   // uniform: scalar loads
+    const f4 me = f4{mq.x, mq.y, mq.z, 0.0f};
+    const int np = static_cast<int>(n);
+    int32_t *sel = sels[wv];
+    TopK top{picks[wv], k, np};
     if (finite3(me.x, me.y, me.z)) {
-        uint64_t thr = kNone;                                                // the KP-th key (uniform)
-        // candidates of the next step are loaded before the current step is tested
-        int64_t j = lane;
-        f4 pj = j < n ? f4{pos[j * 3], pos[j * 3 + 1], pos[j * 3 + 2], 0.0f} : f4{0.0f, 0.0f, 0.0f, 0.0f};
-        for (int64_t c0 = 0; c0 < n; c0 += kWave) {
-            const f4 cur = pj;
-            const int64_t jc = c0 + lane;
-            j = jc + kWave;
-            if (j < n) pj = f4{pos[j * 3], pos[j * 3 + 1], pos[j * 3 + 2], 0.0f};
-            const float d2 = sqdist(me, cur);
-            uint64_t key = (static_cast<uint64_t>(__float_as_uint(d2)) << 32) | static_cast<uint32_t>(jc);
-            key = (jc >= n || jc == q) ? ~0ull : key;   // past the end, or the query itself
-            insert_lanes(__builtin_amdgcn_ballot_w64(key < thr), key, KP, L, thr);
+        for (int c0 = 0; c0 < np; c0 += kAhead * kWave) {
+            P3 p[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int j = c0 + u * kWave + lane;
+                p[u] = pts[j < np ? j : q];
+            }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int j = c0 + u * kWave + lane;
+                top.offer(sqdist(me, f4{p[u].x, p[u].y, p[u].z, 0.0f}), j, j < np && j != q);
+            }
         }
     }
-    const bool has = lane < k && L < kNone;
-    const int32_t sel = has ? static_cast<int32_t>(static_cast<uint32_t>(L)) : -1;
-    if (far_count) {
-        if (lane < kMaxK) sels[wv][lane] = sel;
-        lds_fence();
-        put_query(sels[wv], q, k, feat, lane, kWave, x, y, nbr);
+    top.shrink(k);
+    top.select(sel);
+    if (n > kTreeMax) {
+        put_query(sel, q, k, feat, lane, kWave, x, y, nbr);
         return;
     }
-    if (nbr && lane < k) nbr[q * k + lane] = sel;
+    const int32_t j = lane < k ? sel[lane] : -1;
+    if (nbr && lane < k) nbr[static_cast<int64_t>(q) * k + lane] = j;
     for (int f = 0; f < feat; ++f) {
-        float v = has ? x[static_cast<int64_t>(sel) * feat + f] : 0.0f;
+        float v = j >= 0 ? x[static_cast<int64_t>(j) * feat + f] : 0.0f;
         // fixed shuffle tree over the lanes (the selected rows in key order, then zeros)
 #pragma unroll
         for (int o = kWave / 2; o >= 1; o /= 2) v += __shfl_xor(v, o);
-        if (lane == 0) y[q * feat + f] = v;
+        if (lane == 0) y[static_cast<int64_t>(q) * feat + f] = v;
     }
 }
 
-template <int KP>
 int launch_brute(int64_t n, int k, int feat, const float *pos, const float *x, float *y, int32_t *nbr,
                  hipStream_t stream, const SegCount *far_count = nullptr, const int2 *far = nullptr,
                  const f4 *rec = nullptr) {
     if (!far) prof_before(stream);
-    hipLaunchKernelGGL(brute_kernel<KP>, dim3(static_cast<unsigned>(ceil_div(n, kBruteWaves))),
-                       dim3(kBruteWaves * kWave), 0, stream, pos, n, k, feat, x, y, nbr, far_count, far, rec);
+    hipLaunchKernelGGL(brute_kernel, dim3(static_cast<unsigned>(ceil_div(n, kBruteWaves))), dim3(kBruteWaves * kWave),
+                       0, stream, pos, n, k, feat, x, y, nbr, far_count, far, rec);
     if (!far) prof_after(stream);
     return check_launch("kNN brute force");
 }
@@ -932,18 +1137,7 @@ size_t workspace_bytes(int64_t n) {
 
 int forward(int64_t n, int32_t feat, const float *pos, const float *x, int32_t k, float *y, int32_t *nbr, void *ws,
             hipStream_t stream) {
-    const int kp = k <= 1 ? 1 : k <= 2 ? 2 : k <= 4 ? 4 : k <= 8 ? 8 : k <= 16 ? 16 : 32;
-    auto brute = [&](const SegCount *far_count, const int2 *far, const f4 *rec) {
-        switch (kp) {
-            case 1: return launch_brute<1>(n, k, feat, pos, x, y, nbr, stream, far_count, far, rec);
-            case 2: return launch_brute<2>(n, k, feat, pos, x, y, nbr, stream, far_count, far, rec);
-            case 4: return launch_brute<4>(n, k, feat, pos, x, y, nbr, stream, far_count, far, rec);
-            case 8: return launch_brute<8>(n, k, feat, pos, x, y, nbr, stream, far_count, far, rec);
-            case 16: return launch_brute<16>(n, k, feat, pos, x, y, nbr, stream, far_count, far, rec);
-            default: return launch_brute<32>(n, k, feat, pos, x, y, nbr, stream, far_count, far, rec);
-        }
-    };
-    if (n <= kBruteMax) return brute(nullptr, nullptr, nullptr);
+    if (n <= kBruteMax) return launch_brute(n, k, feat, pos, x, y, nbr, stream);
     Carve c(ws);
     Ws w = carve(c, n);
     const int np = static_cast<int>(ceil_div(n, kBlock) < kPartials ? ceil_div(n, kBlock) : kPartials);
@@ -966,9 +1160,11 @@ int forward(int64_t n, int32_t feat, const float *pos, const float *x, int32_t k
                        w.start, w.seg_count);
     if (int rc = check_launch("kNN cells")) return rc;
     prof_before(stream);
-    hipLaunchKernelGGL(cell_select_kernel, dim3(static_cast<unsigned>(ceil_div(n, kQueries * (kBlock / kWave)))),
-                       dim3(kBlock), 0, stream, w.curve, w.start, w.rec, w.key_sorted, n, k, feat, x, y, nbr,
-                       w.seg_count, w.seg, w.seg_count + kSegs, w.far);
+    const int queries = n < kFewQueries ? 2 : kQueries;
+    hipLaunchKernelGGL((n < kFewQueries ? cell_select_kernel<2> : cell_select_kernel<kQueries>),
+                       dim3(static_cast<unsigned>(ceil_div(n, queries * (kBlock / kWave)))), dim3(kBlock), 0, stream,
+                       w.curve, w.start, w.rec, w.key_sorted, n, k, feat, x, y, nbr, w.seg_count, w.seg,
+                       w.seg_count + kSegs, w.far);
     prof_after(stream);
     if (int rc = check_launch("kNN cell select")) return rc;
     // persistent grids: how many queries are listed is known on the device only
@@ -979,7 +1175,7 @@ int forward(int64_t n, int32_t feat, const float *pos, const float *x, int32_t k
     hipLaunchKernelGGL(wide_select_kernel, dim3(static_cast<unsigned>(wb)), dim3(kBlock), 0, stream, w.curve, w.start,
                        w.rec, w.key_sorted, n, k, feat, x, y, nbr, w.seg_count, w.seg, w.seg_count + kSegs, w.far);
     if (int rc = check_launch("kNN wide select")) return rc;
-    if (n <= kBruteFar) return brute(w.seg_count + kSegs, w.far, w.rec);
+    if (n <= kBruteFar) return launch_brute(n, k, feat, pos, x, y, nbr, stream, w.seg_count + kSegs, w.far, w.rec);
     const int64_t fb = far_blocks * cus < most ? far_blocks * cus : most;
     hipLaunchKernelGGL(stream_select_kernel, dim3(static_cast<unsigned>(fb)), dim3(kBlock), 0, stream, w.curve,
                        w.start, w.rec, w.key_sorted, n, k, feat, x, y, nbr, w.seg_count + kSegs, w.far);

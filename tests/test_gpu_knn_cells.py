@@ -42,6 +42,8 @@ def points(kind, n):
             p[a * 2500: (a + 1) * 2500] = rng.random(3) + 1e-6 * rng.random((2500, 3))
         p[-9:] *= 50.0
         return p.astype(np.float32)
+    if kind == "copies":      # more equal keys than a wavefront has lanes, at every query
+        return np.repeat(rng.random((n // 90 + 1, 3)), 90, 0)[rng.permutation(n)].astype(np.float32)
     if kind == "lattice":     # more than 64 equal distances at many keys
         return synth.binary_grid_points(n, 3, (98, n), span=20)
     return cloud(kind, n, 3)
@@ -55,7 +57,7 @@ def test_clouds(lib, kind, k):
 
 
 @pytest.mark.parametrize("kind", ["uniform", "box", "outlier", "same", "far", "tiny", "holes", "lattice", "line",
-                                  "grid", "cluster", "flat", "clumps", "many holes"])
+                                  "grid", "cluster", "flat", "clumps", "many holes", "copies"])
 @pytest.mark.parametrize("n,k", [(16385, 1), (16385, 16), (20001, 32)])
 def test_clouds_behind_the_streaming_scan(lib, kind, n, k):
     # above 16,384 points the queries that the other scans leave open are streamed
@@ -65,6 +67,26 @@ def test_clouds_behind_the_streaming_scan(lib, kind, n, k):
     check(lib, pos, 1, k, pts=pts)
 
 
+@pytest.mark.parametrize("kind", ["uniform", "box", "outlier", "same", "far", "tiny", "holes", "lattice", "line",
+                                  "grid", "cluster", "flat", "clumps", "many holes", "copies"])
+@pytest.mark.parametrize("k", [1, 16, 32])
+def test_clouds_above_the_scan_of_every_point(lib, kind, k):
+    check(lib, points(kind, 11600), 1, k)
+
+
+@pytest.mark.parametrize("n", [200, 2500])
+@pytest.mark.parametrize("kind", ["same", "copies", "line", "holes"])
+@pytest.mark.parametrize("k", [0, 1, 17, 32])
+def test_scan_of_every_point(lib, kind, n, k):
+    check(lib, points(kind, n), 1, k)
+
+
+@pytest.mark.parametrize("n", [11000, 11001, 11004, 16384, 23999, 24000])
+@pytest.mark.parametrize("k,F", [(0, 1), (5, 0), (17, 9), (31, 3)])
+def test_sizes_at_the_bounds(lib, n, k, F):
+    check(lib, points("uniform", n), F, k)
+
+
 @pytest.mark.parametrize("n", [7168, 7169, 7176, 9001])
 @pytest.mark.parametrize("k,F", [(0, 1), (5, 0), (17, 9), (31, 3)])
 def test_sizes(lib, n, k, F):
@@ -72,7 +94,7 @@ def test_sizes(lib, n, k, F):
 
 
 @pytest.mark.parametrize("kind", ["uniform", "cluster", "outlier"])
-@pytest.mark.parametrize("n", [7169, 12000, 17000])
+@pytest.mark.parametrize("n", [7169, 11001, 12000, 17000])
 def test_sums_are_added_in_key_order(lib, kind, n):
     # above 7,168 points, whichever scan decides a query; the clump and the outlier reach all of them
     pos, k = points(kind, n), 32
