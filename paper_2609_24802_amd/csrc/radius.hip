@@ -11,7 +11,7 @@
 // destinations (radius_tile.hip); wider rows, and row arrays of 4 GiB and
 // more, with one wavefront per destination cell (below), whose 27 neighbour
 // cells are 9 contiguous runs of the cell-ordered arrays (x-adjacent cells are
-// adjacent in memory).  Rows of 8 lanes with two units each.
+// adjacent in memory).
 #include "csr_common.hpp"
 #include "radius.hpp"
 #include "radius_cells.hpp"
@@ -446,9 +446,12 @@ __device__ __forceinline__ void cell_consume(const Params &p, const int32_t *__r
 }
 
 // y_i = sum_j k_ij x_j; K floats per unit, LPR lanes per row, UPL units per
-// lane per feature block.
+// lane per feature block. The pair loop is latency-bound, so the one-unit
+// forms are held to 72 registers (7 waves per SIMD instead of 6); the few
+// values this spills cost less than the extra wave gains. The two-unit form
+// would spill dozens and keeps its registers.
 template <int K, int LPR, int UPL>
-__global__ __launch_bounds__(kBlock) void radius_fwd_cell_kernel(const Params *__restrict__ prm,
+__global__ __launch_bounds__(kBlock, UPL == 1 ? 7 : 1) void radius_fwd_cell_kernel(const Params *__restrict__ prm,
                                                                  const int32_t *__restrict__ order,
                                                                  uint32_t *__restrict__ sched,
                                                                  const int64_t *__restrict__ start,
@@ -832,6 +835,20 @@ int fwd_cell(int64_t fu, const Ws &w, const float *x, float r2, float nis, float
     return check_launch("radius forward");
 }
 
+// Lanes per row: the smallest power of two covering the row's units, at most
+// 8 (with two units per lane beyond that); wider rows loop over feature blocks.
+// The narrow forms serve row arrays of 4 GiB and more, whose byte offsets the
+// tiles do not hold.
+template <int K>
+int fwd_units(int64_t fu, const Ws &w, const float *x, float r2, float nis, float *y, int32_t *count,
+              hipStream_t stream) {
+    if (fu <= 1) return fwd_cell<K, 1, 1>(fu, w, x, r2, nis, y, count, stream);
+    if (fu <= 2) return fwd_cell<K, 2, 1>(fu, w, x, r2, nis, y, count, stream);
+    if (fu <= 4) return fwd_cell<K, 4, 1>(fu, w, x, r2, nis, y, count, stream);
+    if (fu <= 8) return fwd_cell<K, 8, 1>(fu, w, x, r2, nis, y, count, stream);
+    return fwd_cell<K, 8, 2>(fu, w, x, r2, nis, y, count, stream);
+}
+
 struct BwdIo {
     const float *pos, *x, *dy;
     float *dx, *dp;
@@ -846,6 +863,15 @@ int bwd_cell(int64_t fu, const Ws &w, const BwdIo &io, float r2, float nis, floa
                        w.order, w.sched, w.start, w.rec, io.pos, io.x, io.dy, fu, r2, nis, tis, io.dx, io.dp);
     prof_after(stream);
     return check_launch("radius backward");
+}
+
+template <int K, bool DX, bool DP>
+int bwd_units(int64_t fu, const Ws &w, const BwdIo &io, float r2, float nis, float tis, hipStream_t stream) {
+    if (fu <= 1) return bwd_cell<K, 1, 1, DX, DP>(fu, w, io, r2, nis, tis, stream);
+    if (fu <= 2) return bwd_cell<K, 2, 1, DX, DP>(fu, w, io, r2, nis, tis, stream);
+    if (fu <= 4) return bwd_cell<K, 4, 1, DX, DP>(fu, w, io, r2, nis, tis, stream);
+    if (fu <= 8) return bwd_cell<K, 8, 1, DX, DP>(fu, w, io, r2, nis, tis, stream);
+    return bwd_cell<K, 8, 2, DX, DP>(fu, w, io, r2, nis, tis, stream);
 }
 
 // The consume kernels index feature units with 32-bit arithmetic.
@@ -888,8 +914,8 @@ int forward(int64_t n, int32_t feat, const float *pos, const float *x, float rad
     const float nis = -1.0f / (sigma * sigma) * kLog2e;  // weights are exp2(d2 * nis)
     if (tiles)
         return tile_forward(n, feat, Cells{w.prm, w.start, w.rec}, w.cell_sorted, x, r2, nis, y, count, stream);
-    if (vec) return fwd_cell<4, 8, 2>(fu, w, x, r2, nis, y, count, stream);
-    return fwd_cell<1, 8, 2>(fu, w, x, r2, nis, y, count, stream);
+    if (vec) return fwd_units<4>(fu, w, x, r2, nis, y, count, stream);
+    return fwd_units<1>(fu, w, x, r2, nis, y, count, stream);
 }
 
 int backward(int64_t n, int32_t feat, const float *pos, const float *x, float radius, float sigma, const float *dy,
@@ -909,9 +935,9 @@ int backward(int64_t n, int32_t feat, const float *pos, const float *x, float ra
                              stream);
     const BwdIo io{pos, x, dy, dx, dpos};
 #define TIGA_B(KK)                                                                  \
-    if (dx && dpos) return bwd_cell<KK, 8, 2, true, true>(fu, w, io, r2, nis, tis, stream); \
-    if (dx) return bwd_cell<KK, 8, 2, true, false>(fu, w, io, r2, nis, tis, stream);        \
-    return bwd_cell<KK, 8, 2, false, true>(fu, w, io, r2, nis, tis, stream)
+    if (dx && dpos) return bwd_units<KK, true, true>(fu, w, io, r2, nis, tis, stream); \
+    if (dx) return bwd_units<KK, true, false>(fu, w, io, r2, nis, tis, stream);        \
+    return bwd_units<KK, false, true>(fu, w, io, r2, nis, tis, stream)
     if (vec) {
         TIGA_B(4);
     } else {

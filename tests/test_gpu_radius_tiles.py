@@ -112,3 +112,32 @@ def test_denormal_rows(lib, F):
     y, _ = lib.tiga_mp_radius_fwd(dev(pos), dev(x), 0.2, 1e18)
     ry, _, _ = oracle.radius_fwd(pos, x, 0.2, 1e18)
     assert np.array_equal(host(y).astype(np.float64), ry)
+
+
+@pytest.mark.parametrize("F", [32, 16, 5])
+def test_row_arrays_of_4_gib(lib, F):
+    # their byte offsets pass 32 bits, so one wavefront per cell with its lists takes them; the same columns in narrower
+    # arrays go by tiles
+    n = (1 << 30) // F + 3
+    g = torch.Generator(device="cuda").manual_seed(F)
+    pos = torch.rand(n, 3, generator=g, device="cuda")
+    x, dy = (torch.randn(n, F, generator=g, device="cuda") for _ in range(2))
+    r = float((5.0 * 3 / (4 * np.pi * n)) ** (1 / 3))
+    s = 0.6 * r
+    y, cnt = lib.tiga_mp_radius_fwd(pos, x, r, s)
+    dx, dp = lib.tiga_mp_radius_bwd(pos, x, dy, r, s)
+    dp_sum, dp_mag = (torch.zeros_like(dp) for _ in range(2))
+    for cols in (slice(0, F // 2), slice(F // 2, F)):
+        xs, dys = x[:, cols].contiguous(), dy[:, cols].contiguous()
+        ya, ca = lib.tiga_mp_radius_fwd(pos, xs.abs(), r, s)
+        dxa, _ = lib.tiga_mp_radius_fwd(pos, dys.abs(), r, s)
+        # |p_j - p_i| < r in the sum of the position gradient's terms
+        dp_mag += (2 * r / s ** 2) * ((ya * dys.abs()).sum(1) + (dxa * xs.abs()).sum(1))[:, None]
+        yt, ct = lib.tiga_mp_radius_fwd(pos, xs, r, s)
+        assert torch.equal(ct, cnt) and torch.equal(ca, cnt)
+        assert bool(((y[:, cols] - yt).abs() <= 1e-5 * ya).all())
+        dxt, dpt = lib.tiga_mp_radius_bwd(pos, xs, dys, r, s)
+        assert bool(((dx[:, cols] - dxt).abs() <= 1e-5 * dxa).all())
+        dp_sum += dpt
+        del xs, dys, ya, dxa, yt, dxt, dpt
+    assert bool(((dp - dp_sum).abs() <= 1e-5 * dp_mag).all())
