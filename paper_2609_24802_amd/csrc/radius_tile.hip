@@ -3,9 +3,9 @@
 // A wavefront owns 16 consecutive cell-ordered points.  Lane (g, m), g = lane / 16, m = lane % 16, tests
 // destination m against the candidates of its group g, so the 16 destinations share every candidate row and
 // no list of accepted pairs is built:
-//   - the points of a tile that lie in one x-row of cells form a segment (nearly always the whole tile; a
-//     tile that crosses the end of a row has two); the segment's candidates are the 9 runs of cells around
-//     its x-range;
+//   - the points of a tile that lie in one x-row of cells, with no more than kGap cells from one to the next, form
+//     a segment (nearly always the whole tile; a tile that crosses the end of a row has two); the segment's
+//     candidates are the 9 runs of cells around its x-range, all of them in cells next to a point's;
 //   - a candidate is kept (LDS list: position, byte offset of its feature row) when the box of the segment's
 //     destinations is within the radius of it: about 186 of 350 for uniform points with cells of the
 //     radius.  The box distance is formed with the predicate's own operations, and every rounding is
@@ -37,6 +37,11 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kTile = 16;
 constexpr int kList = 256;   // candidates between two passes
+// Cells from one point of a segment to the next, at most: the runs around them then leave no cell between.  Without
+// this bound the few points of a sparse row of cells had a dense row beside it for candidates, whole: 1M points on
+// a line, 16 of them one cell beside it, forward of 1 and 32 features 18 and 27 ms, now 0.18 and 0.25 ms (lists that
+// test cell by cell: 0.31 and 0.36 ms).
+constexpr int kGap = 3;
 
 struct alignas(16) Work {
     f32x4 list[kList];       // x, y, z, byte offset of the row (bits)
@@ -108,19 +113,23 @@ __device__ __forceinline__ void for_tile(const Params &p, const int64_t *__restr
     dst.in = valid;
     pass(static_cast<int>(n - s0 < kTile ? n - s0 : kTile), std::true_type{});
     lds_fence();
-    const int cx = cell % p.dim[0], row = cell / p.dim[0];
-    uint32_t todo = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(valid)) & 0xffffu;
+    const uint32_t dx = p.dim[0], dy = p.dim[1], ucell = cell;   // unsigned divisions are the shorter ones
+    // cells ascend along the tile: bit m of `ends` where point m is a segment's last
+    const uint32_t all = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(valid)) & 0xffffu;
+    const int step = __builtin_amdgcn_update_dpp(0, cell, 0x101, 0xf, 0xf, true) - cell;   // of lane m + 1's cell
+    const bool last = step > kGap || static_cast<int>(ucell % dx) + step >= p.dim[0];
+    const uint32_t ends = (static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(last)) | ~(all >> 1)) & all;
+    uint32_t todo = all;
     const float inf = __builtin_inff();
     while (todo) {
-        const int f = __builtin_ctz(todo);
-        const int srow = __builtin_amdgcn_readlane(row, f);
-        dst.in = valid && row == srow;
-        const uint32_t seg = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(dst.in)) & 0xffffu;
-        todo &= ~seg;
-        // cells ascend along the tile: the segment's x-range, one cell more on each side
-        const int x0 = __builtin_amdgcn_readlane(cx, f), x1 = __builtin_amdgcn_readlane(cx, 31 - __builtin_clz(seg));
+        const int f = __builtin_ctz(todo), l = __builtin_ctz(todo & ends);
+        const int first_cell = __builtin_amdgcn_readlane(cell, f), srow = static_cast<uint32_t>(first_cell) / dx;
+        dst.in = m >= f && m <= l;
+        todo &= ~0u << (l + 1);
+        // the segment's x-range, one cell more on each side
+        const int x0 = first_cell - srow * p.dim[0], x1 = x0 + (__builtin_amdgcn_readlane(cell, l) - first_cell);
         const int xa = x0 > 0 ? x0 - 1 : 0, xb = x1 + 1 < p.dim[0] ? x1 + 1 : p.dim[0] - 1;
-        const int cy = srow % p.dim[1], cz = srow / p.dim[1];
+        const int cz = static_cast<uint32_t>(srow) / dy, cy = srow - cz * p.dim[1];
         // box of the segment's destinations (records of non-finite points are all +inf: within the radius of
         // nothing)
         const bool box = dst.in && finite(dst.x);
@@ -243,7 +252,8 @@ __device__ void slow_row(const Params &p, const int64_t *__restrict__ start, con
 // lane m holds the features NB m .. NB m + NB - 1 of a row in one load (VEC: feat a multiple of NB), or the
 // features m, m + 16, ... (any feat).
 template <int NB, int SF, bool VEC, bool CNT>
-__global__ __launch_bounds__(kBlock) void tile_fwd_kernel(const Params *__restrict__ prm,
+__global__ __launch_bounds__(kBlock, NB == 0 && SF == 1 ? 8 : 1)   // one feature: 8 wavefronts per SIMD hide its loads
+    void tile_fwd_kernel(const Params *__restrict__ prm,
                                                           const int64_t *__restrict__ start,
                                                           const f32x4 *__restrict__ rec,
                                                           const int32_t *__restrict__ cells, int64_t n, int feat,

@@ -55,7 +55,7 @@ def test_sizes(lib, n):
         check(lib, pos, F, 0.4, 0.3)
 
 
-@pytest.mark.parametrize("kind", ["thin", "dense", "line", "grid"])
+@pytest.mark.parametrize("kind", ["thin", "dense", "line", "grid", "gaps"])
 def test_clouds(lib, kind):
     rng = np.random.default_rng(4)
     pos = rng.random((900, 3)).astype(np.float32)
@@ -66,6 +66,11 @@ def test_clouds(lib, kind):
         pos[:600] = pos[:600] * np.float32(0.2) + np.float32(0.4)
     elif kind == "line":
         pos[:, 1:] = 0.5
+    elif kind == "gaps":     # rows of few points beside a dense one: gaps of every width between a tile's points
+        pos[:, 1:] *= np.float32(0.1)
+        pos[:, 0] *= 9
+        pos[:60, 1] += np.float32(0.13)
+        pos[60:75, 1] += np.float32(0.26)
     else:                    # coincident points and distances equal to the radius
         pos = (rng.integers(0, 9, (900, 3)) / 8).astype(np.float32)
         r = 0.125
