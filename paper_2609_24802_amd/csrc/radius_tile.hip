@@ -13,7 +13,7 @@
 //   - each lane evaluates the exact predicate and the weight of its pairs (0 if rejected), which is the A
 //     operand of v_mfma_f32_16x16x4_f32 as it stands: the weighted sum over candidates is a matrix product
 //     with the candidates' rows (read in place, 16 lanes on one row) on the matrix cores, in fp32.  Rows of
-//     up to 4 features are summed by the vector units instead, from values kept in the list.
+//     one or two features are summed by the vector units instead, from values kept in LDS.
 //   - Backward: dx is the same product with dy; the inner products <dy_i, x_j> + <dy_j, x_i> of the tile
 //     with 16 candidates are two more products, whose result has lane (g, m) hold its own pairs' values.
 // The matrix product also multiplies rejected pairs' rows by zero, which a non-finite row would turn into
@@ -248,6 +248,44 @@ __device__ void slow_row(const Params &p, const int64_t *__restrict__ start, con
     });
 }
 
+// Weighted sums over the candidates as matrix products, NB blocks of 16 features.  Each of a lane group's four
+// candidates per step has accumulators of its own (NB = 1; the even and the odd ones otherwise, where more would cost a
+// wavefront per SIMD), which are added in 64 bits.  Distance from 64 bits (norms of difference and result), 31
+// neighbours, 16 and 32 features: 8.1e-8 and 9.8e-8, in one run of roundings 1.21e-7, as trees over lane groups (the
+// lists' sums) 9.1e-8 and 1.10e-7.  Times before and now, 1M points of degree 32: 16 features 272 and 287 us, 32
+// features 358 and 361 us (whole calls).
+template <int NB>
+struct Sums {
+    static constexpr int A = NB == 1 ? 4 : 2;
+    f32x4 a[A][NB];
+    __device__ __forceinline__ Sums() {
+#pragma unroll
+        for (int i = 0; i < A; ++i)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) a[i][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+    __device__ __forceinline__ void add(int s, float w, const float (&v)[NB]) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+            a[s % A][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(w, v[b], a[s % A][b], 0, 0, 0);
+    }
+    // whether all are finite
+    __device__ __forceinline__ bool total(f32x4 (&out)[NB]) const {
+        bool ok = true;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                double v = static_cast<double>(a[0][b][r]) + a[1][b][r];
+                if constexpr (A == 4) v += static_cast<double>(a[2][b][r]) + a[3][b][r];
+                out[b][r] = static_cast<float>(v);
+                ok &= finite(out[b][r]);
+            }
+        }
+        return ok;
+    }
+};
+
 // Forward.  NB = 0: rows of SF features, summed by the vector units.  NB > 0: NB blocks of 16 features;
 // lane m holds the features NB m .. NB m + NB - 1 of a row in one load (VEC: feat a multiple of NB), or the
 // features m, m + 16, ... (any feat).
@@ -275,12 +313,10 @@ __global__ __launch_bounds__(kBlock, NB == 0 && SF == 1 ? 8 : 1)   // one featur
         const int f = VEC ? NB * m : m + 16 * b;
         fo[b] = static_cast<uint32_t>(f < feat ? f : (VEC ? feat - NB : feat - 1)) * 4;
     }
-    f32x4 acc[AB];
+    Sums<AB> acc;
+    float sum[AS][2];   // like acc
 #pragma unroll
-    for (int b = 0; b < AB; ++b) acc[b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    float sum[AS];
-#pragma unroll
-    for (int f = 0; f < AS; ++f) sum[f] = 0.0f;
+    for (int f = 0; f < AS; ++f) sum[f][0] = sum[f][1] = 0.0f;
     int deg = 0;
     Dst dst;
     int32_t id;
@@ -326,13 +362,11 @@ __global__ __launch_bounds__(kBlock, NB == 0 && SF == 1 ? 8 : 1)   // one featur
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 if constexpr (NB > 0) {
-#pragma unroll
-                    for (int b = 0; b < NB; ++b)
-                        acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s], xv[s][b], acc[b], 0, 0, 0);
+                    acc.add(s, w[s], xv[s]);
                 } else {
 #pragma unroll
                     for (int f = 0; f < AS; ++f)
-                        if (near[s]) sum[f] = fmaf(w[s], vals[wv][f][j + 4 * g + s], sum[f]);
+                        if (near[s]) sum[f][s & 1] = fmaf(w[s], vals[wv][f][j + 4 * g + s], sum[f][s & 1]);
                 }
             }
         };
@@ -350,17 +384,14 @@ __global__ __launch_bounds__(kBlock, NB == 0 && SF == 1 ? 8 : 1)   // one featur
     if constexpr (NB == 0) {
 #pragma unroll
         for (int f = 0; f < AS; ++f) {
-            sum[f] += shfl_xor_f(sum[f], 16);
-            sum[f] += shfl_xor_f(sum[f], 32);
-            if (lane < kTile && id >= 0) y[static_cast<int64_t>(id) * AS + f] = sum[f];
+            double v = static_cast<double>(sum[f][0]) + sum[f][1];
+            v += __shfl_xor(v, 16, kWave);
+            v += __shfl_xor(v, 32, kWave);
+            if (lane < kTile && id >= 0) y[static_cast<int64_t>(id) * AS + f] = static_cast<float>(v);
         }
     } else {
-        bool bad = false;
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) bad |= !finite(acc[b][r]);
-        if (__any(bad)) {
+        f32x4 out[AB];
+        if (__any(!acc.total(out))) {
             for (int64_t s = s0; s < s0 + kTile && s < n; ++s) {
                 float a = 0.0f;
                 slow_row(p, start, rec, s, row_bytes, r2, nis, [&](uint32_t off, float w, const float (&)[3]) {
@@ -376,13 +407,13 @@ __global__ __launch_bounds__(kBlock, NB == 0 && SF == 1 ? 8 : 1)   // one featur
             if (row < 0) continue;
             float *o = y + row * feat;
             if constexpr (VEC && NB == 2) {
-                if (2 * m < feat) put_bytes(o + 2 * m, make_float2(acc[0][r], acc[1][r]));
+                if (2 * m < feat) put_bytes(o + 2 * m, make_float2(out[0][r], out[1][r]));
             } else if constexpr (VEC && NB == 4) {
-                if (4 * m < feat) put_bytes(o + 4 * m, make_float4(acc[0][r], acc[1][r], acc[2][r], acc[3][r]));
+                if (4 * m < feat) put_bytes(o + 4 * m, make_float4(out[0][r], out[1][r], out[2][r], out[3][r]));
             } else {
 #pragma unroll
                 for (int b = 0; b < NB; ++b)
-                    if (m + 16 * b < feat) o[m + 16 * b] = acc[b][r];
+                    if (m + 16 * b < feat) o[m + 16 * b] = out[b][r];
             }
         }
     }
@@ -402,8 +433,10 @@ __device__ __forceinline__ void load_part(const float *__restrict__ base, uint32
 // in one load; where those would pass the row's end it takes the row's last KS, and the destinations' operand
 // is 0 for the features that another group has (KS <= feat).  dx is summed in NB blocks of 16 features (PAIR:
 // even feat, two adjacent features per lane).
+// Wavefronts per SIMD are asked for where the accumulators would cost one (1M points, 32 features, whole calls: 707 us
+// with the 4, 793 us with 3; 16 features spill with 5: 510 us, 468 us with 4).
 template <int KS, bool PAIR, bool DX, bool DP>
-__global__ __launch_bounds__(kBlock) void tile_bwd_kernel(const Params *__restrict__ prm,
+__global__ __launch_bounds__(kBlock, DX && DP ? (KS >= 4 ? 4 : 5) : 1) void tile_bwd_kernel(const Params *__restrict__ prm,
                                                           const int64_t *__restrict__ start,
                                                           const f32x4 *__restrict__ rec,
                                                           const int32_t *__restrict__ cells, int64_t n, int feat,
@@ -425,9 +458,7 @@ __global__ __launch_bounds__(kBlock) void tile_bwd_kernel(const Params *__restri
         fo[b] = static_cast<uint32_t>(f < feat ? f : (PAIR ? feat - 2 : feat - 1)) * 4;
     }
     const int part = KS * g + KS <= feat ? KS * g : feat - KS;   // this group's first feature
-    f32x4 acc[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) acc[b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    Sums<NB> acc;
     float gp[3] = {0.0f, 0.0f, 0.0f};
     // the destinations' rows, as operands of the inner products
     float yi[KS], xi[KS];
@@ -477,26 +508,31 @@ __global__ __launch_bounds__(kBlock) void tile_bwd_kernel(const Params *__restri
                 if (!FULL && (i >= cnt || (own && i == m))) w[s] = 0.0f;
             }
             if constexpr (DP) {
-                f32x4 a = {0.0f, 0.0f, 0.0f, 0.0f}, b = {0.0f, 0.0f, 0.0f, 0.0f};
+                // both products of 4 features add to the same accumulator, of several for shorter runs of roundings:
+                // the position gradient of 32 features ends 1.38e-7 from 64 bits, 1.50e-7 with two accumulators (the
+                // lists: 1.45e-7); a fourth costs 3% of the time
+                constexpr int A = KS == 8 ? 3 : KS;
+                f32x4 a[A];
 #pragma unroll
                 for (int t = 0; t < KS; ++t) {
-                    a = __builtin_amdgcn_mfma_f32_16x16x4f32(xj[t], yi[t], a, 0, 0, 0);
-                    b = __builtin_amdgcn_mfma_f32_16x16x4f32(yj[t], xi[t], b, 0, 0, 0);
+                    const f32x4 c = t < A ? f32x4{0.0f, 0.0f, 0.0f, 0.0f} : a[t % A];
+                    a[t % A] = __builtin_amdgcn_mfma_f32_16x16x4f32(xj[t], yi[t], c, 0, 0, 0);
+                    a[t % A] = __builtin_amdgcn_mfma_f32_16x16x4f32(yj[t], xi[t], a[t % A], 0, 0, 0);
                 }
+                if constexpr (A >= 2) a[0] += a[1];
+                if constexpr (A == 3) a[0] += a[2];
+                if constexpr (A == 4) a[0] += a[2] + a[3];
                 // lane (g, m), register s: candidate j + 4 g + s with destination m
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
-                    const float cc = tis * w[s] * (a[s] + b[s]);
+                    const float cc = tis * w[s] * a[0][s];
 #pragma unroll
                     for (int q = 0; q < 3; ++q) gp[q] = fmaf(cc, diff[s][q], gp[q]);
                 }
             }
             if constexpr (DX) {
 #pragma unroll
-                for (int s = 0; s < 4; ++s)
-#pragma unroll
-                    for (int b = 0; b < NB; ++b)
-                        acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s], gv[s][b], acc[b], 0, 0, 0);
+                for (int s = 0; s < 4; ++s) acc.add(s, w[s], gv[s]);
             }
         };
         int j = 0;
@@ -506,12 +542,8 @@ __global__ __launch_bounds__(kBlock) void tile_bwd_kernel(const Params *__restri
     };
     for_tile(p, start, rec, cells, n, s0, row_bytes, r2, wk, dst, id, [](int, uint32_t) {}, pass);
     bool bad = false;
-    if constexpr (DX) {
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) bad |= !finite(acc[b][r]);
-    }
+    f32x4 out[NB];
+    if constexpr (DX) bad |= !acc.total(out);
     if constexpr (DP) {
 #pragma unroll
         for (int q = 0; q < 3; ++q) bad |= !finite(gp[q]);
@@ -544,9 +576,10 @@ __global__ __launch_bounds__(kBlock) void tile_bwd_kernel(const Params *__restri
     if constexpr (DP) {
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
-            gp[q] += shfl_xor_f(gp[q], 16);
-            gp[q] += shfl_xor_f(gp[q], 32);
-            if (lane < kTile && id >= 0) dp[static_cast<int64_t>(id) * 3 + q] = gp[q];
+            double v = static_cast<double>(gp[q]);
+            v += __shfl_xor(v, 16, kWave);
+            v += __shfl_xor(v, 32, kWave);
+            if (lane < kTile && id >= 0) dp[static_cast<int64_t>(id) * 3 + q] = static_cast<float>(v);
         }
     }
     if constexpr (DX) {
@@ -556,11 +589,11 @@ __global__ __launch_bounds__(kBlock) void tile_bwd_kernel(const Params *__restri
             if (row < 0) continue;
             float *o = dx + row * feat;
             if constexpr (PAIR) {
-                if (2 * m < feat) put_bytes(o + 2 * m, make_float2(acc[0][r], acc[1][r]));
+                if (2 * m < feat) put_bytes(o + 2 * m, make_float2(out[0][r], out[1][r]));
             } else {
 #pragma unroll
                 for (int b = 0; b < NB; ++b)
-                    if (m + 16 * b < feat) o[m + 16 * b] = acc[b][r];
+                    if (m + 16 * b < feat) o[m + 16 * b] = out[b][r];
             }
         }
     }

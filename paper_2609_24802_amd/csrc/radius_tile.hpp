@@ -1,4 +1,5 @@
-// Consuming kernels of the radius relation on tiles of 16 destinations (rows of up to kTileFeat features).
+// Consuming kernels of the radius relation on tiles of 16 destinations (rows of up to kTileFeatFwd features forward,
+// kTileFeatBwd backward).
 #pragma once
 
 #include "radius_cells.hpp"

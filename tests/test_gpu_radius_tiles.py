@@ -146,3 +146,20 @@ def test_row_arrays_of_4_gib(lib, F):
         dp_sum += dpt
         del xs, dys, ya, dxa, yt, dxt, dpt
     assert bool(((dp - dp_sum).abs() <= 1e-5 * dp_mag).all())
+
+
+@pytest.mark.parametrize("F", [1, 4, 8, 15, 16, 31, 32])
+def test_distance_from_64_bits(lib, F):
+    # 31 neighbours of a point: summed in one run of roundings they end 1.2e-7 (norms of difference and result) from
+    # 64 bits and the position gradient 1.5e-7; as trees over lane groups at most 1.1e-7, and 1.0e-7 and 1.4e-7 here
+    n = 30000
+    rng = np.random.default_rng(F)
+    pos = rng.random((n, 3)).astype(np.float32)
+    x, dy = (rng.standard_normal((n, F)).astype(np.float32) for _ in range(2))
+    r = float(np.float32((31 * 3 / (4 * np.pi * n)) ** (1 / 3)))
+    y, _ = lib.tiga_mp_radius_fwd(dev(pos), dev(x), r, 0.5 * r)
+    dx, dp = lib.tiga_mp_radius_bwd(dev(pos), dev(x), dev(dy), r, 0.5 * r)
+    ry = oracle.radius_fwd(pos, x, r, 0.5 * r)[0]
+    rdx, _, rdp, _ = oracle.radius_bwd(pos, x, dy, r, 0.5 * r)
+    for name, a, b, most in (("y", y, ry, 1.1e-7), ("dx", dx, rdx, 1.1e-7), ("dpos", dp, rdp, 1.45e-7)):
+        assert np.linalg.norm(host(a).astype(np.float64) - b) < most * np.linalg.norm(b), name
