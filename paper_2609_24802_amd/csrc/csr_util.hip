@@ -9,30 +9,34 @@ namespace csr {
 namespace {
 
 // rec[e] = (bits of w[e], or of 1.0 without weights; the destination row of e).  Block b takes the edges
-// [b * kRecEdges, (b + 1) * kRecEdges), so hub rows cost no more than others (split by tiles of rows, the
+// [b * kBlock * ITEMS, (b + 1) * kBlock * ITEMS), so hub rows cost no more than others (split by tiles of rows, the
 // 16 blocks of a tile with a 320,000-edge row set the time: 162 us for 16M edges).  It stages windows of
-// kRecRows row pointers, each starting at the row of the first edge not yet written (found by a search
-// over row_ptr by one wavefront, 64 probes per step), so runs of empty rows are skipped; a thread finds
-// the rows of its edges by binary search in LDS, kRecItems edges at a time (independent chains).
+// kRecRows row pointers, each starting within 64 rows before that of the first edge not yet written (found by a
+// search over row_ptr by one wavefront, 64 probes per step; a short row_ptr is staged whole), so runs of empty
+// rows are skipped; a thread finds the rows of its edges by binary search in LDS, ITEMS edges at a time
+// (independent chains): 8 where that gives every compute unit two blocks, 1 below (8,192 edges of 1,024 rows: 8.6 us
+// in 4 blocks, 3.6 us in 32; 500,000 edges 7 us with one; 1.2M edges 13 us with 8, 15 us with one).
 // Bound: the 8-byte writes and the 4-byte reads of w.
 constexpr int kRecRows = 1024;
 constexpr int kRecItems = 8;
-constexpr int kRecEdges = kBlock * kRecItems;
+constexpr int kRecBlocks = 2;   // per compute unit
 
+template <int ITEMS>
 __global__ __launch_bounds__(kBlock) void edge_records_kernel(const int64_t *__restrict__ row_ptr, int64_t nrows,
                                                               int64_t nedges, const float *__restrict__ w,
                                                               int2 *__restrict__ rec) {
+    constexpr int kEdges = kBlock * ITEMS;
     __shared__ int64_t sp[kRecRows + 1];
     __shared__ int64_t first_row;
-    const int64_t e1 = static_cast<int64_t>(blockIdx.x + 1) * kRecEdges < nedges
-                           ? static_cast<int64_t>(blockIdx.x + 1) * kRecEdges
+    const int64_t e1 = static_cast<int64_t>(blockIdx.x + 1) * kEdges < nedges
+                           ? static_cast<int64_t>(blockIdx.x + 1) * kEdges
                            : nedges;
     int64_t r_known = 0;   // row_ptr[r_known] <= the next edge
-    for (int64_t e0 = static_cast<int64_t>(blockIdx.x) * kRecEdges; e0 < e1;) {
+    for (int64_t e0 = static_cast<int64_t>(blockIdx.x) * kEdges; e0 < e1;) {
         if (threadIdx.x < kWave) {
-            // last row r with row_ptr[r] <= e0: [lo, lo + len) holds it, row_ptr[lo] <= e0
+            // [lo, lo + len) holds the last row r with row_ptr[r] <= e0; row_ptr[lo] <= e0
             int64_t lo = r_known, len = nrows - r_known;
-            while (len > 1) {
+            while (len > kWave && nrows > kRecRows) {
                 const int64_t step = (len + kWave - 1) / kWave;
                 const int64_t at = lo + step * lane_id();
                 const bool below = at < lo + len && row_ptr[at] <= e0;
@@ -51,18 +55,18 @@ __global__ __launch_bounds__(kBlock) void edge_records_kernel(const int64_t *__r
         __syncthreads();
         const int64_t end = sp[nr] < e1 ? sp[nr] : e1;   // > e0: row r0 holds e0
         if (end <= e0) return;                           // (unless row_ptr ends before num_edges)
-        int lo[kRecItems];
+        int lo[ITEMS];
 #pragma unroll
-        for (int k = 0; k < kRecItems; ++k) lo[k] = 0;
+        for (int k = 0; k < ITEMS; ++k) lo[k] = 0;
         // the last row i of the window with sp[i] <= e: descending powers of two
         for (int step = kRecRows / 2; step >= 1; step >>= 1)
 #pragma unroll
-            for (int k = 0; k < kRecItems; ++k) {
+            for (int k = 0; k < ITEMS; ++k) {
                 const int i = lo[k] + step;
                 if (i < nr && sp[i] <= e0 + k * kBlock + threadIdx.x) lo[k] = i;
             }
 #pragma unroll
-        for (int k = 0; k < kRecItems; ++k) {
+        for (int k = 0; k < ITEMS; ++k) {
             const int64_t e = e0 + k * kBlock + threadIdx.x;
             if (e < end) rec[e] = make_int2(__float_as_int(w ? w[e] : 1.0f), static_cast<int32_t>(r0 + lo[k]));
         }
@@ -141,8 +145,10 @@ int launch_transpose(const tiga_csr *rel, int64_t *src_ptr, int32_t *edge_id, vo
 
 int launch_edge_records(const tiga_csr *rel, const float *w, int2 *rec, hipStream_t stream) {
     if (rel->num_edges == 0 || rel->num_dst == 0) return TIGA_OK;
-    hipLaunchKernelGGL(edge_records_kernel, dim3(static_cast<unsigned>(ceil_div(rel->num_edges, kRecEdges))),
-                       dim3(kBlock), 0, stream, rel->row_ptr, rel->num_dst, rel->num_edges, w, rec);
+    const bool few = ceil_div(rel->num_edges, kBlock * kRecItems) < kRecBlocks * device_cus();
+    const unsigned blocks = static_cast<unsigned>(ceil_div(rel->num_edges, few ? kBlock : kBlock * kRecItems));
+    hipLaunchKernelGGL((few ? edge_records_kernel<1> : edge_records_kernel<kRecItems>), dim3(blocks), dim3(kBlock), 0,
+                       stream, rel->row_ptr, rel->num_dst, rel->num_edges, w, rec);
     return check_launch("edge records");
 }
 

@@ -50,3 +50,13 @@ def test_large_plan_tile(lib, rows):
                                                      p=[.3, .3, .2, .15, .045, .005])
     deg[[0, 8191, 8192, rows - 1]] = [30_000, 17, 2049, 33]
     check(lib, deg, 1000, 4, "sum", 7)
+
+
+@pytest.mark.parametrize("rows", [1, 700, 1024, 1025, 1090, 5000])
+@pytest.mark.parametrize("edges", [1, 255, 257, 2049, 9000, 2048 * 511, 2048 * 511 + 1, 2048 * 600 + 7])
+def test_edge_records(lib, rows, edges):
+    # one and eight edges per thread (the latter from 512 blocks of 2,048 edges on), whole and windowed row pointers,
+    # empty rows before, between and after the others
+    rng = np.random.default_rng(rows + edges)
+    deg = np.bincount(rng.choice(rng.permutation(rows)[: max(1, rows // 3)], edges), minlength=rows)
+    check(lib, deg, 50, 4, "sum", 11)
