@@ -57,10 +57,10 @@ struct GatherBody {
         using A = Acc<K, RED>;
         const int s = glane / L;
         const int l = glane % L;
-        for (int64_t fb = 0; fb < t.fu; fb += L) {
-            const int32_t f0 = static_cast<int32_t>(fb + l) * K;
+        for (int32_t fb = 0; fb < t.feat; fb += L * K) {
+            const int32_t f0 = fb + l * K;
             const bool uok = f0 < t.feat;
-            const int32_t f = unit_float<K>(fb + l, t.feat);
+            const int32_t f = unit_float<K>(fb / K + l, t.feat);
             A acc;
             acc.init();
             if constexpr (DW) {
@@ -93,16 +93,15 @@ struct GatherBody {
     }
 };
 
+// At most 96 scalar registers: with the trap handler's 16 a SIMD's 800 then hold 7 wavefronts.  With more it holds
+// 6, which the occupancy query does not say, and the seventh share of the persistent grid ran alone after the others
+// (3 features, max, 1M rows, 16M edges: 346 us, 280 us now).
 template <int K, int L, int RED, int WM, bool BUF, bool NT, bool DW>
-__global__ __launch_bounds__(kBlock) void gather_reduce_kernel(Trav t, int64_t n_groups,
-                                                               const Desc *__restrict__ chunks,
-                                                               const PlanCounts *__restrict__ counts,
-                                                               float *__restrict__ out,
-                                                               int32_t *__restrict__ out_arg,
-                                                               float *__restrict__ part_v,
-                                                               int32_t *__restrict__ part_e,
-                                                               const float *__restrict__ hx,
-                                                               float *__restrict__ hdw) {
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(96)))
+    void gather_reduce_kernel(Trav t, int64_t n_groups, const Desc *__restrict__ chunks,
+                              const PlanCounts *__restrict__ counts, float *__restrict__ out,
+                              int32_t *__restrict__ out_arg, float *__restrict__ part_v, int32_t *__restrict__ part_e,
+                              const float *__restrict__ hx, float *__restrict__ hdw) {
     const Table<K, BUF, NT> tab(t.table, t.feat, t.table_bytes);
     // argmax table (max-routing gather only; otherwise an unused empty resource)
     const __amdgpu_buffer_rsrc_t ars = __builtin_amdgcn_make_buffer_rsrc(
@@ -217,11 +216,10 @@ template <int K, int L, int RED, int WM, bool BUF, bool NT, bool DW>
 int launch_gather_reduce(const Trav &t, int64_t n_groups, const PlanWs &w, const PlanBounds &b, float *out,
                          int32_t *out_arg, const EdgeGrad &eg, hipStream_t stream) {
     auto kern = gather_reduce_kernel<K, L, RED, WM, BUF, NT, DW>;
-    // at most 7 wavefronts per SIMD of 16-byte gathers: with 8 they slow each other down (1M rows of 64 features,
-    // 16M edges: 717 us with 7, 860 us with 8).  Rows of up to 3 floats take what is resident (500,000 rows, 8M
-    // edges, 3 features, max: 113 us, with 7 155 us).
+    // at most 7 wavefronts per SIMD, which is what the scalar registers allow (1M rows of 64 features, 16M edges: 717 us,
+    // with a grid for 8 860 us; 1 feature 119 and 125 us)
     static const int resident = resident_blocks(reinterpret_cast<const void *>(kern), kBlock);
-    static const int per_cu = K == 1 || resident < 7 ? resident : 7;
+    static const int per_cu = resident < 7 ? resident : 7;
     const int blocks = persistent_blocks(n_groups + b.max_chunks, per_cu);
     prof_before(stream);
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(kBlock), 0, stream, t, n_groups, w.chunks, w.counts, out, out_arg,
