@@ -7,8 +7,8 @@
 //     a segment (nearly always the whole tile; a tile that crosses the end of a row has two); the segment's
 //     candidates are the 9 runs of cells around its x-range, all of them in cells next to a point's;
 //   - a candidate is kept (LDS list: position, byte offset of its feature row) when the box of the segment's
-//     destinations is within the radius of it: about 186 of 350 for uniform points with cells of the
-//     radius.  The box distance is formed with the predicate's own operations, and every rounding is
+//     destinations is within the radius of it: 205 of 331 (1M uniform points of degree 32, cells of the
+//     radius).  The box distance is formed with the predicate's own operations, and every rounding is
 //     monotone, so no accepted pair is dropped;
 //   - each lane evaluates the exact predicate and the weight of its pairs (0 if rejected), which is the A
 //     operand of v_mfma_f32_16x16x4_f32 as it stands: the weighted sum over candidates is a matrix product
@@ -24,8 +24,8 @@
 // to the kernel's time), at twice the rate of plain fused multiply-adds.  Per 16 candidates a wavefront issues 53
 // vector and 8 matrix instructions (forward, 32 features).
 // Measured against the previous kernels, which tested one cell's destinations in turn and appended accepted pairs
-// to LDS lists (kept for wider rows): 1M uniform points, mean degree 31, 32 features 345 -> 262 us forward and
-// 810 -> 740 us backward; 131,072 points, 1 feature 50 -> 27 us; 300,000 points of a normal cloud (whole calls,
+// to LDS lists (kept for wider rows): 1M uniform points, mean degree 31, 32 features 345 -> 281 us forward and
+// 810 -> 737 us backward; 131,072 points, 1 feature 50 -> 25 us; 300,000 points of a normal cloud (whole calls,
 // 32 features) 1,771 -> 215 us and 2,376 -> 374 us, since a dense cell is now many wavefronts' work.
 #include "radius_tile.hpp"
 
