@@ -32,7 +32,7 @@
 //  instructions per pair of compacted candidates.  131,072 points of unequal density, k = 16, whole calls,
 //  tiles and now: a third in a clump of 0.002 2,173 and 796 us, normal 507 and 378 us, one far outlier
 //  3,375 and 328 us, 100 copies of each position 231 and 206 us.  At k = 4, clusters whose finest cells are
-//  below the table are still slower than the tiles were (50 clusters: 258 and 317 us).
+//  below the table are still slower than the tiles were (50 clusters: 253 and 353 us).
 #include "knn.hpp"
 
 #include <cmath>
@@ -538,7 +538,6 @@ __device__ __forceinline__ void rank_picks(Pick &pk, int m, int k, int32_t *__re
 template <int B>
 __device__ __forceinline__ bool pick_query(Pick &pk, const float (&d2)[B], const int (&id)[B], float reach, int k,
                                            int n, int32_t *__restrict__ sel) {
-    const int lane = lane_id();
     auto within = [&](float r) __attribute__((always_inline)) {
         int m = 0;
 #pragma unroll
@@ -1043,6 +1042,10 @@ __global__ __launch_bounds__(kBlock, 4) void stream_select_kernel(const Curve *_
 // 9,000 points, uniform 57 and 74 us, normal 55 and 128 us; 11,000 points, uniform 73 and 76 us; 12,000 points,
 // uniform 84 and 75 us.
 constexpr int64_t kBruteMax = 11000;
+// For few neighbours, whose cells gain less: 12,000 points, k = 4, without the build and with it, uniform 73 and 70 us, a
+// third of them in a clump 88 and 156 us, normal 83 and 121 us.
+constexpr int kFewK = 8;
+constexpr int64_t kBruteMaxFewK = 12500;
 // Up to this many points the queries that the wider scan leaves undecided scan every point too.
 constexpr int64_t kBruteFar = 16384;
 constexpr int64_t kTreeMax = 7168;   // sums of at most so many points are pairwise trees
@@ -1137,7 +1140,7 @@ size_t workspace_bytes(int64_t n) {
 
 int forward(int64_t n, int32_t feat, const float *pos, const float *x, int32_t k, float *y, int32_t *nbr, void *ws,
             hipStream_t stream) {
-    if (n <= kBruteMax) return launch_brute(n, k, feat, pos, x, y, nbr, stream);
+    if (n <= (k <= kFewK ? kBruteMaxFewK : kBruteMax)) return launch_brute(n, k, feat, pos, x, y, nbr, stream);
     Carve c(ws);
     Ws w = carve(c, n);
     const int np = static_cast<int>(ceil_div(n, kBlock) < kPartials ? ceil_div(n, kBlock) : kPartials);

@@ -69,9 +69,9 @@ def test_clouds_behind_the_streaming_scan(lib, kind, n, k):
 
 @pytest.mark.parametrize("kind", ["uniform", "box", "outlier", "same", "far", "tiny", "holes", "lattice", "line",
                                   "grid", "cluster", "flat", "clumps", "many holes", "copies"])
-@pytest.mark.parametrize("k", [1, 16, 32])
-def test_clouds_above_the_scan_of_every_point(lib, kind, k):
-    check(lib, points(kind, 11600), 1, k)
+@pytest.mark.parametrize("n,k", [(12501, 1), (11600, 16), (11600, 32)])
+def test_clouds_above_the_scan_of_every_point(lib, kind, n, k):
+    check(lib, points(kind, n), 1, k)
 
 
 @pytest.mark.parametrize("n", [200, 2500])
@@ -81,8 +81,8 @@ def test_scan_of_every_point(lib, kind, n, k):
     check(lib, points(kind, n), 1, k)
 
 
-@pytest.mark.parametrize("n", [11000, 11001, 11004, 16384, 23999, 24000])
-@pytest.mark.parametrize("k,F", [(0, 1), (5, 0), (17, 9), (31, 3)])
+@pytest.mark.parametrize("n", [11000, 11001, 11004, 12500, 12501, 16384, 23999, 24000])
+@pytest.mark.parametrize("k,F", [(0, 1), (5, 0), (8, 2), (9, 1), (17, 9), (31, 3)])
 def test_sizes_at_the_bounds(lib, n, k, F):
     check(lib, points("uniform", n), F, k)
 
